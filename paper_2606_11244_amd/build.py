@@ -27,6 +27,13 @@ COMMON = ["-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
           f"-I{os.path.join(ROOT, 'include')}", f"-I{CSRC}"]
 
+# the kernel files compile once per code width (SPEAR_WB) and activation dtype
+UNITS = tuple((src, f"w{wb}_{'bf16' if bf else 'f16'}",
+               [f"--offload-arch={ARCH}", "-x", "hip", f"-DSPEAR_WB={wb}", f"-DSPEAR_BF16_UNIT={bf}"])
+              for src in ("spear_kernels.hip", "spear_gemm.hip") for wb in (4, 3) for bf in (0, 1)) + (
+    ("spear_api.cpp", "", [f"--offload-arch={ARCH}", "-x", "hip"]),
+    ("spear_sched.cpp", "", [f"--offload-arch={ARCH}"]))
+
 
 def _run(cmd):
     r = subprocess.run(cmd, capture_output=True, text=True)
@@ -38,17 +45,12 @@ def _run(cmd):
 
 def build(verbose: bool = False) -> str:
     """Compile every HIP/C++ source of the library (in parallel processes) and
-    link libspear.so. spear_kernels.hip is compiled twice: for 4-bit and for
-    3-bit weight codes (SPEAR_WB). The measured-ceiling kernels go into
+    link libspear.so. The measured-ceiling kernels go into
     libspear_ceiling.so."""
     objdir = os.path.join(HERE, "_build")
     os.makedirs(objdir, exist_ok=True)
-    units = (("spear_kernels.hip", "w4", [f"--offload-arch={ARCH}", "-x", "hip", "-DSPEAR_WB=4"]),
-             ("spear_kernels.hip", "w3", [f"--offload-arch={ARCH}", "-x", "hip", "-DSPEAR_WB=3"]),
-             ("spear_api.cpp", "", [f"--offload-arch={ARCH}", "-x", "hip"]),
-             ("spear_sched.cpp", "", [f"--offload-arch={ARCH}"]))
     cmds, objs = [], []
-    for src, tag, extra in units:
+    for src, tag, extra in UNITS:
         obj = os.path.join(objdir, src + (("." + tag) if tag else "") + ".o")
         cmd = [HIPCC] + COMMON + extra + ["-c", os.path.join(CSRC, src), "-o", obj]
         if verbose:

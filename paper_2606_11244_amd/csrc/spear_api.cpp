@@ -818,11 +818,10 @@ hipError_t launch_gemv_wb(const Resolved& z, int epi, const GemvParams& p, int g
                           size_t lds, hipStream_t st) {
   // the naive chain's 4-bit kernel and grouped launches keep two stages
   const int nst = epi == EPI_NONE || epi == EPI_READY || epi == EPI_FUSED ? z.nst : 2;
-  return z.wb == 3 ? launch_gemv_w3(z.dt, z.MT, z.RT, epi, nst, p, grid, block, lds, st)
-                   : launch_gemv_w4(z.dt, z.MT, z.RT, epi, nst, p, grid, block, lds, st);
+  return SPEAR_BY_WB(launch_gemv, z.wb, z.dt)(z.MT, z.RT, epi, nst, p, grid, block, lds, st);
 }
 hipError_t launch_gemm_wb(const Resolved& z, int epi, const GemmParams& p, hipStream_t st) {
-  return z.wb == 3 ? launch_gemm_w3(z.dt, epi, p, st) : launch_gemm_w4(z.dt, epi, p, st);
+  return SPEAR_BY_WB(launch_gemm, z.wb, z.dt)(epi, p, st);
 }
 
 // res: [M][N] act-dtype residual added before the output's single rounding, or null
@@ -883,7 +882,7 @@ spear_status_t run_layer(const spear_problem_t* prob, const Resolved& z, const v
       e.vl = (uint16_t*)(ws + z.off_vl);
       e.v = nullptr;
     }
-    st = hip_status(launch_ec(z.dt, e, ec_grid, z.ec_block, z.ec_ipp, z.lds_prod, s));
+    st = hip_status(SPEAR_BY_DT(launch_ec, z.dt)(e, ec_grid, z.ec_block, z.ec_ipp, z.lds_prod, s));
     if (st != SPEAR_OK) return st;
     if (z.gemv) {
       GemvParams g = make_gemv(prob, z, x, w, y, ec, ws);
@@ -905,14 +904,14 @@ spear_status_t run_layer(const spear_problem_t* prob, const Resolved& z, const v
     if ((st = side_stream(&ss)) != SPEAR_OK) return st;
     if (hipEventRecord(ss->fork, s) != hipSuccess || hipStreamWaitEvent(ss->s, ss->fork, 0) != hipSuccess)
       return SPEAR_E_HIP;
-    st = hip_status(launch_ec(z.dt, e, ec_grid, z.ec_block, z.ec_ipp, z.lds_prod, ss->s));
+    st = hip_status(SPEAR_BY_DT(launch_ec, z.dt)(e, ec_grid, z.ec_block, z.ec_ipp, z.lds_prod, ss->s));
     if (st != SPEAR_OK) return st;
     if (hipEventRecord(ss->join, ss->s) != hipSuccess) return SPEAR_E_HIP;
     st = run_w4(prob, z, x, w, y, ws, s, res);
     if (st != SPEAR_OK) return st;
     if (hipStreamWaitEvent(s, ss->join, 0) != hipSuccess) return SPEAR_E_HIP;
     const bool i8o = ab_int8(ec);
-    return hip_status(launch_ec_up_acc(z.dt, e.v, i8o ? nullptr : (const uint16_t*)ec->B,
+    return hip_status(SPEAR_BY_DT(launch_ec_up_acc, z.dt)(e.v, i8o ? nullptr : (const uint16_t*)ec->B,
                                        i8o ? (const int8_t*)ec->B : nullptr,
                                        i8o ? ec->b_scale : nullptr, (uint16_t*)y, (int)prob->M,
                                        (int)prob->N, z.r, s));
@@ -921,12 +920,12 @@ spear_status_t run_layer(const spear_problem_t* prob, const Resolved& z, const v
   st = run_w4(prob, z, x, w, y, ws, s, res);
   if (st != SPEAR_OK) return st;
   e.u_out = (float*)(ws + z.off_u);
-  st = hip_status(launch_ec(z.dt, e, ec_grid, z.ec_block, z.ec_ipp, z.lds_prod, s));
+  st = hip_status(SPEAR_BY_DT(launch_ec, z.dt)(e, ec_grid, z.ec_block, z.ec_ipp, z.lds_prod, s));
   if (st != SPEAR_OK) return st;
-  st = hip_status(launch_gate(z.dt, e, z.ntb, z.lds_gate, s));
+  st = hip_status(SPEAR_BY_DT(launch_gate, z.dt)(e, z.ntb, z.lds_gate, s));
   if (st != SPEAR_OK) return st;
   const bool i8 = ab_int8(ec);
-  return hip_status(launch_ec_up_acc(z.dt, e.v, i8 ? nullptr : (const uint16_t*)ec->B,
+  return hip_status(SPEAR_BY_DT(launch_ec_up_acc, z.dt)(e.v, i8 ? nullptr : (const uint16_t*)ec->B,
                                      i8 ? (const int8_t*)ec->B : nullptr, i8 ? ec->b_scale : nullptr,
                                      (uint16_t*)y, (int)prob->M, (int)prob->N, z.r, s));
 }
@@ -1107,7 +1106,7 @@ spear_status_t spear_w4ec_linear_tail(const spear_problem_t* prob, const void* x
   hipStream_t s = (hipStream_t)hip_stream;
   st = run_layer(prob, z, x, w, ec, y, (const uint16_t*)tail->residual, (char*)workspace, s);
   if (st != SPEAR_OK || !tail->norm_w) return st;
-  return hip_status(launch_rmsnorm(z.dt, (const uint16_t*)y, (const uint16_t*)tail->norm_w,
+  return hip_status(SPEAR_BY_DT(launch_rmsnorm, z.dt)((const uint16_t*)y, (const uint16_t*)tail->norm_w,
                                    tail->eps, (uint16_t*)tail->y_norm, (int)prob->M,
                                    (int)prob->N, s));
 }
@@ -1306,9 +1305,7 @@ spear_status_t spear_w4ec_linear_group(int32_t n, const spear_layer_call_t* call
   }
   g.n = k;
   const Resolved& z0 = z[first];
-  return hip_status(z0.wb == 3
-                        ? launch_gemv_group_w3(z0.dt, z0.MT, z0.RT, epi, g, 64 * z0.NW, lds, s)
-                        : launch_gemv_group_w4(z0.dt, z0.MT, z0.RT, epi, g, 64 * z0.NW, lds, s));
+  return hip_status(SPEAR_BY_WB(launch_gemv_group, z0.wb, z0.dt)(z0.MT, z0.RT, epi, g, 64 * z0.NW, lds, s));
 }
 
 spear_status_t spear_w4_dequant(const spear_problem_t* prob, const spear_w4_t* w, void* w_out,
@@ -1329,9 +1326,9 @@ spear_status_t spear_w4_dequant(const spear_problem_t* prob, const spear_w4_t* w
       overlaps(w_out, outb, w->scales, (size_t)prob->N * (prob->K / G) * 2) ||
       overlaps(w_out, outb, w->zeros, (size_t)prob->N * (prob->K / G)))
     return SPEAR_E_ALIAS;
-  const auto dq = prob->weight_bits == 3 ? launch_dequant_w3 : launch_dequant_w4;
-  return hip_status(dq(prob->act_dtype, w->qweight, w->scales, w->zeros, (uint16_t*)w_out,
-                       (int)prob->N, (int)prob->K, G, (hipStream_t)hip_stream));
+  return hip_status(SPEAR_BY_WB(launch_dequant, prob->weight_bits, prob->act_dtype)(
+      w->qweight, w->scales, w->zeros, (uint16_t*)w_out, (int)prob->N, (int)prob->K, G,
+      (hipStream_t)hip_stream));
 }
 
 spear_status_t spear_workspace_regions(const spear_problem_t* prob, int32_t with_ec,

@@ -229,28 +229,35 @@ __host__ __device__ inline size_t ec_block_lds(int NW, int R1p, int h, int r) {
   return ec_red_bytes(NW) + ec_lds_bytes(R1p, h, r);
 }
 
-// The kernels that read packed codes come in a 4-bit (_w4) and a 3-bit (_w3)
-// build of spear_kernels.hip; the others only in the 4-bit one.
+// The launchers exist per activation dtype (_f16, _bf16) and, for the kernels
+// that read packed codes, per code width (_w4, _w3).
 #define SPEAR_WEIGHT_LAUNCHERS(W)                                                                 \
-  hipError_t launch_dequant_##W(int dt, const uint32_t* qw, const uint16_t* sc,                 \
-                                const uint8_t* zr, uint16_t* out, int N, int K, int G,          \
-                                hipStream_t st);                                                \
-  hipError_t launch_gemv_##W(int dt, int MT, int RT, int epi, int nst, const GemvParams& p,     \
-                             int grid, int block, size_t lds, hipStream_t st);                  \
-  hipError_t launch_gemv_group_##W(int dt, int MT, int RT, int epi, const GemvGroup& g,         \
-                                   int block, size_t lds, hipStream_t st);                      \
-  hipError_t launch_gemm_##W(int dt, int epi, const GemmParams& p, hipStream_t st);
-SPEAR_WEIGHT_LAUNCHERS(w4)
-SPEAR_WEIGHT_LAUNCHERS(w3)
+  hipError_t launch_dequant_##W(const uint32_t* qw, const uint16_t* sc, const uint8_t* zr,      \
+                                uint16_t* out, int N, int K, int G, hipStream_t st);            \
+  hipError_t launch_gemv_##W(int MT, int RT, int epi, int nst, const GemvParams& p, int grid,   \
+                             int block, size_t lds, hipStream_t st);                            \
+  hipError_t launch_gemv_group_##W(int MT, int RT, int epi, const GemvGroup& g, int block,      \
+                                   size_t lds, hipStream_t st);                                 \
+  hipError_t launch_gemm_##W(int epi, const GemmParams& p, hipStream_t st);
+#define SPEAR_ACT_LAUNCHERS(D)                                                                    \
+  hipError_t launch_ec_##D(const EcParams& e, int grid, int block, int ipp, size_t lds,          \
+                           hipStream_t st);                                                      \
+  hipError_t launch_gate_##D(const EcParams& e, int ntb, size_t lds, hipStream_t st);            \
+  /* y_norm[m] = RMSNorm(y[m]) * w (one workgroup per token row) */                              \
+  hipError_t launch_rmsnorm_##D(const uint16_t* y, const uint16_t* w, float eps,                 \
+                                uint16_t* y_norm, int M, int N, hipStream_t st);                 \
+  hipError_t launch_ec_up_acc_##D(const float* v, const uint16_t* B, const int8_t* B8,           \
+                                  const float* sb, uint16_t* y, int M, int N, int r,             \
+                                  hipStream_t st);                                               \
+  SPEAR_WEIGHT_LAUNCHERS(w4_##D)                                                                 \
+  SPEAR_WEIGHT_LAUNCHERS(w3_##D)
+SPEAR_ACT_LAUNCHERS(f16)
+SPEAR_ACT_LAUNCHERS(bf16)
+#undef SPEAR_ACT_LAUNCHERS
 #undef SPEAR_WEIGHT_LAUNCHERS
-hipError_t launch_ec(int dt, const EcParams& e, int grid, int block, int ipp, size_t lds,
-                     hipStream_t st);
+// the launcher of a dtype, or of a code width and a dtype
+#define SPEAR_BY_DT(name, dt) ((dt) == DT_F16 ? name##_f16 : name##_bf16)
+#define SPEAR_BY_WB(name, wb, dt) ((wb) == 3 ? SPEAR_BY_DT(name##_w3, dt) : SPEAR_BY_DT(name##_w4, dt))
 bool gemv_shape_supported(int MT, int RT);
-hipError_t launch_gate(int dt, const EcParams& e, int ntb, size_t lds, hipStream_t st);
-// y_norm[m] = RMSNorm(y[m]) * w (one workgroup per token row)
-hipError_t launch_rmsnorm(int dt, const uint16_t* y, const uint16_t* w, float eps, uint16_t* y_norm,
-                          int M, int N, hipStream_t st);
-hipError_t launch_ec_up_acc(int dt, const float* v, const uint16_t* B, const int8_t* B8,
-                            const float* sb, uint16_t* y, int M, int N, int r, hipStream_t st);
 
 }  // namespace spear
