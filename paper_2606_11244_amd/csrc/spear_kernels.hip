@@ -334,8 +334,68 @@ __global__ __launch_bounds__(256) void k_ec_up_acc(const float* __restrict__ v,
 
 // Post-EC tail, next-layer RMSNorm: y_norm[m][n] = y[m][n] * rsqrt(mean_n y[m][n]^2
 // + eps) * w[n] over the stored (rounded) row, in fp32, one rounding. One
-// workgroup of 256 threads per token row; the sum of squares is reduced in a
-// fixed order (per-thread strided sums, then a tree in LDS).
+// workgroup per token row; the sum of squares is reduced in a fixed order.
+//
+// Rows of a multiple of eight elements: at decode the kernel is one memory
+// round trip and a reduction, at prefill a copy. Each thread takes C 16-byte
+// chunks of the row (chunk c * threads + tid), all loaded together with the
+// norm weights and kept in registers for the second pass, and the reduction
+// is a butterfly per wave and one exchange of the wave sums, one barrier.
+// (Two-byte loads in a strided loop, one round trip per element and a
+// barrier per tree level took 16.0 us for an 8192-wide row at one token and
+// 47 at 4096 tokens; this takes 4.3 us, of which about 3 are the launch and
+// the first byte, and about 20.)
+template <int DT, int C>
+__global__ __launch_bounds__(1024) void k_rmsnorm_v(const uint16_t* __restrict__ y,
+                                                    const uint16_t* __restrict__ w, float eps,
+                                                    uint16_t* __restrict__ y_norm, int N) {
+  __shared__ float red[16];
+  const int tid = threadIdx.x, nthr = blockDim.x, n8 = N >> 3;
+  const uint16_t* yr = y + (size_t)blockIdx.x * N;
+  u32x4 v[C], wv[C];
+#pragma unroll
+  for (int c = 0; c < C; ++c) {
+    const int i = c * nthr + tid;
+    v[c] = i < n8 ? ldg16(yr + 8 * i) : u32x4{0, 0, 0, 0};
+  }
+#pragma unroll
+  for (int c = 0; c < C; ++c) {
+    const int i = c * nthr + tid;
+    wv[c] = i < n8 ? ldg16(w + 8 * i) : u32x4{0, 0, 0, 0};
+  }
+  float ss = 0.f;
+#pragma unroll
+  for (int c = 0; c < C; ++c)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const float lo = act2f<DT>(v[c][q] & 0xFFFFu), hi = act2f<DT>(v[c][q] >> 16);
+      ss += lo * lo;
+      ss += hi * hi;
+    }
+#pragma unroll
+  for (int h = 32; h > 0; h >>= 1) ss += __shfl_xor(ss, h);
+  if ((tid & 63) == 0) red[tid >> 6] = ss;
+  __syncthreads();
+  ss = 0.f;
+  for (int i = 0; i < nthr >> 6; ++i) ss += red[i];
+  const float scale = 1.f / sqrtf(ss / (float)N + eps);
+  uint16_t* out = y_norm + (size_t)blockIdx.x * N;
+#pragma unroll
+  for (int c = 0; c < C; ++c) {
+    const int i = c * nthr + tid;
+    u32x4 o;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const float lo = act2f<DT>(v[c][q] & 0xFFFFu) * scale * act2f<DT>(wv[c][q] & 0xFFFFu);
+      const float hi = act2f<DT>(v[c][q] >> 16) * scale * act2f<DT>(wv[c][q] >> 16);
+      o[q] = (uint32_t)f2act<DT>(lo) | ((uint32_t)f2act<DT>(hi) << 16);
+    }
+    if (i < n8) *(u32x4*)(out + 8 * i) = o;
+  }
+}
+
+// Any other row length: 256 threads, element by element (per-thread strided
+// sums, then a tree in LDS).
 template <int DT>
 __global__ __launch_bounds__(256) void k_rmsnorm(const uint16_t* __restrict__ y,
                                                  const uint16_t* __restrict__ w, float eps,
@@ -1381,8 +1441,19 @@ hipError_t SPEAR_D(launch_gate)(const EcParams& e, int ntb, size_t lds, hipStrea
 hipError_t SPEAR_D(launch_rmsnorm)(const uint16_t* y, const uint16_t* w, float eps, uint16_t* y_norm,
                           int M, int N, hipStream_t st) {
   if (M == 0 || N == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_rmsnorm<DTC>, dim3(M), dim3(256), 0, st, y, w, eps,
-                                         y_norm, N);
+  // rows of whole 16-byte chunks (the buffers are 16-byte aligned): the
+  // fewest threads, at least 256, that cover the row in four chunks each
+  const int n8 = N / 8;
+  if (N % 8 != 0 || n8 > 4096) {
+    hipLaunchKernelGGL(k_rmsnorm<DTC>, dim3(M), dim3(256), 0, st, y, w, eps, y_norm, N);
+  } else if (n8 <= 256) {
+    hipLaunchKernelGGL((k_rmsnorm_v<DTC, 1>), dim3(M), dim3(256), 0, st, y, w, eps, y_norm, N);
+  } else if (n8 <= 512) {
+    hipLaunchKernelGGL((k_rmsnorm_v<DTC, 2>), dim3(M), dim3(256), 0, st, y, w, eps, y_norm, N);
+  } else {
+    const int thr = n8 <= 1024 ? 256 : n8 <= 2048 ? 512 : 1024;
+    hipLaunchKernelGGL((k_rmsnorm_v<DTC, 4>), dim3(M), dim3(thr), 0, st, y, w, eps, y_norm, N);
+  }
   return hipGetLastError();
 }
 

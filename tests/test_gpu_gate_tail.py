@@ -1,0 +1,48 @@
+"""GPU parity of the row lengths of the post-EC tail's RMSNorm against float64."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2606_11244_amd import synth as S
+
+from gpu_util import log
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+
+
+@pytest.mark.parametrize("N", [8, 20, 2040, 2048, 2056, 4096, 4104, 8192, 8200, 16392, 32768, 32776])
+@pytest.mark.parametrize("dt", [S.F16, S.BF16])
+def test_rmsnorm_row_lengths(N, dt):
+    """Rows of whole 16-byte chunks at every chunk count per thread and its
+    edges, and rows past them (20: not whole chunks; 32776: too long). The
+    norm's own error is one rounding of its inputs' fp32 function, far inside
+    the bar."""
+    from paper_2606_11244_amd import spear as sp
+    L = S.make_layer(M=3, N=N, K=128, group_size=128, rank=0, act_dtype=dt, seed=N)
+    t = S.make_tail(L, seed=1)
+    tdt = sp._TORCH_DT[dt]
+    res = torch.from_numpy(t["residual"].view(np.int16)).view(tdt).cuda()
+    nw = torch.from_numpy(t["norm_w"].view(np.int16)).view(tdt).cuda()
+    dl = sp.DeviceLayer(L)
+    prob = dl.problem()
+    yn = torch.full((3, N), 7.0, dtype=tdt, device="cuda")
+    log(f"rmsnorm N={N} dt={dt}")
+    dl.run_tail(prob, sp.allocate_workspace(prob, False), residual=res, norm_w=nw, eps=t["eps"],
+                y_norm=yn, with_ec=False)
+    torch.cuda.synchronize()
+    y = dl.y.float().cpu().numpy().astype(np.float64)
+    w = S.from_bits(t["norm_w"], dt).astype(np.float64)
+    ref = y / np.sqrt((y * y).mean(axis=1, keepdims=True) + t["eps"]) * w
+    # one rounding to the activation dtype of an fp32 result: half an ulp plus
+    # fp32 noise of the sum (2^-24 per term, relative, on the scale)
+    ulp = 2.0 ** (-11 if dt == S.F16 else -8)
+    got = yn.float().cpu().numpy().astype(np.float64)
+    assert np.all(np.abs(got - ref) <= 1.01 * ulp * np.abs(ref) + 1e-7), np.abs(got - ref).max()
