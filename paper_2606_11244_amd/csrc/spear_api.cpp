@@ -456,7 +456,7 @@ spear_status_t resolve(const spear_problem_t* p, bool with_ec, Resolved* R, int 
       z.ec_mode = path == SPEAR_PATH_UNFUSED_CHAIN ? EC_RAW : EC_LAST;
       z.lds_prod = ec_block_lds(8, z.R1p, z.h, z.r);
     }
-    z.lds_gate = ec_lds_bytes(z.R1p, z.h, z.r);
+    z.lds_gate = ec_lds_bytes(z.R1p, ec_hid_floats(z.h), z.r);
   }
 
   if (z.gemv) {
@@ -476,9 +476,7 @@ spear_status_t resolve(const spear_problem_t* p, bool with_ec, Resolved* R, int 
       if (local) {
         // u [16 MT][R1p] and v [16 MT][r] (and the tanh-MLP gate's hidden
         // layer), the rows of B, the staged A, w_g
-        const size_t hid = z.gate == GATE_TANH ? (size_t)local_tanh_cap((int)M, z.h) * z.h * 4 +
-                                                     (size_t)tanh_stage_halves(z.h, z.r) * 2
-                                               : 0;
+        const size_t hid = z.gate == GATE_TANH ? (size_t)local_tanh_cap((int)M, z.h) * z.h * 4 : 0;
         z.lds_b = (int)align_up(z.lds_e + (size_t)16 * z.MT * (z.R1p + z.r) * 4 + hid, 16);
         z.bpre = (z.r % 8) == 0 && RB * z.r / 8 <= 2 * 64 * z.NW;
         z.lds_a = (int)align_up(z.lds_b + (z.bpre ? (size_t)RB * z.r * 2 : 0), 16);

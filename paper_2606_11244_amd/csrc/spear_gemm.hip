@@ -443,15 +443,13 @@ __global__ __launch_bounds__(128 * TMW, TMW == 2 ? 2 : 1) void k_gemm(GemmParams
     float* v_sh = (float*)(smem + TM * 17 * 4 + 2 * TM * kVS * 2);
     const bool tanh_g = a.gate == GATE_TANH;  // uniform
     if (tanh_g) {
-      // after v: the staged parameters (when they fit), then the hidden layer
+      // after v: the hidden layer
       constexpr int kLds = 2 * (TM + kGemmTN) * LR * 2 + 2 * kGemmEcRows * LR * 2;
-      const int nst = tanh_stage_halves(a.h, a.r);
-      uint16_t* wst = nst > 0 ? (uint16_t*)(v_sh + TM * 16) : nullptr;
-      float* hid = (float*)((char*)(v_sh + TM * 16) + align_up((size_t)nst * 2, 16));
+      float* hid = v_sh + TM * 16;
       const int hid_floats = (kLds - (int)((char*)hid - smem)) / 4;
       const int cap = max(1, min(TM, hid_floats / max(1, a.h)));
       tanh_gate_tokens<DT>(TM, a.r, a.h, u_sh, 17, a.W1, a.b1, a.W2, a.b2, a.alpha, hid, cap,
-                           v_sh, 16, wst);
+                           v_sh, 16);
     }
     for (int idx = tid; idx < TM * kVS; idx += NT) {
       const int t = idx / kVS, j = idx - t * kVS;

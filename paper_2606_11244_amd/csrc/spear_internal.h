@@ -203,30 +203,31 @@ __host__ __device__ inline int local_tanh_cap(int M, int h) {
   const int c = 2048 / (h > 0 ? h : 1);
   return c < 1 ? 1 : (c < M ? c : M);
 }
-// Halves of the tanh-MLP gate's parameters (W1, b1, W2, b2) staged in LDS
-// for the gate, or 0 when they exceed 4096 halves (then read from memory).
-__host__ __device__ inline int tanh_stage_halves(int h, int r) {
-  const int n = 2 * h * r + h + r;
-  return n <= 4096 ? n : 0;
-}
-
 // GEMV workgroups have at most eight waves (a ninth would make the dispatcher
 // reserve three waves' registers on every SIMD and halve residency); the EC
 // variants give one of them to the EC wave.
 constexpr int kGemvMaxThreads = 512;
 
 // LDS of EC work: wave partials red [NW][kEcTiles][64][4] fp32, then
-// u [16][R1p] fp32, hidden [h] fp32 and the v tile [16][r] fp32.
+// u [16][R1p] fp32, hidden [hid] fp32 and the v tile [16][r] fp32. The hidden
+// layer of the tanh-MLP gate takes h floats where one wave runs it a token at
+// a time (the GEMV's fallback) and, where a whole block does, as many tokens
+// at once as 16 KB hold (at least four: h <= 1024).
+__host__ __device__ inline int ec_hid_tokens(int h) {
+  const int c = 4096 / (h > 0 ? h : 1);
+  return c < kTokTile ? c : kTokTile;
+}
+__host__ __device__ inline int ec_hid_floats(int h) { return ec_hid_tokens(h) * h; }
 __host__ __device__ inline size_t ec_red_bytes(int NW) { return (size_t)NW * kEcTiles * 1024; }
 __host__ __device__ inline size_t ec_lds_u_off() { return 0; }
 __host__ __device__ inline size_t ec_lds_hid_off(int R1p) { return align_up((size_t)kTokTile * R1p * 4, 16); }
-__host__ __device__ inline size_t ec_lds_v_off(int R1p, int h) { return ec_lds_hid_off(R1p) + align_up((size_t)h * 4, 16); }
-__host__ __device__ inline size_t ec_lds_bytes(int R1p, int h, int r) {
-  return ec_lds_v_off(R1p, h) + align_up((size_t)kTokTile * (r > 0 ? r : 1) * 4, 16);
+__host__ __device__ inline size_t ec_lds_v_off(int R1p, int hid) { return ec_lds_hid_off(R1p) + align_up((size_t)hid * 4, 16); }
+__host__ __device__ inline size_t ec_lds_bytes(int R1p, int hid, int r) {
+  return ec_lds_v_off(R1p, hid) + align_up((size_t)kTokTile * (r > 0 ? r : 1) * 4, 16);
 }
 // a producer workgroup: red, then the u/hidden/v region
 __host__ __device__ inline size_t ec_block_lds(int NW, int R1p, int h, int r) {
-  return ec_red_bytes(NW) + ec_lds_bytes(R1p, h, r);
+  return ec_red_bytes(NW) + ec_lds_bytes(R1p, ec_hid_floats(h), r);
 }
 
 // The launchers exist per activation dtype (_f16, _bf16) and, for the kernels

@@ -28,7 +28,7 @@ namespace spear {
 // first), so the result does not depend on timing.
 // ---------------------------------------------------------------------------
 template <int DT, int IPP>
-__device__ void ec_project(const EcParams& e, int tb, int it_beg, int it_end, int t_beg, int t_end,
+__device__ __forceinline__ void ec_project(const EcParams& e, int tb, int it_beg, int it_end, int t_beg, int t_end,
                            float* u_lds, float* red) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -140,28 +140,13 @@ __device__ void ec_project(const EcParams& e, int tb, int it_beg, int it_end, in
 // v = alpha * g * u (sigmoid-linear), alpha * (1 + tanh(W2 ReLU(W1 u + b1) + b2)) (.) u
 // (tanh-MLP), or alpha * u (gate one). Ends with a barrier.
 template <int DT>
-__device__ void ec_gate_tile(const EcParams& e, int cnt, const float* u_lds, float* hid,
+__device__ __forceinline__ void ec_gate_tile(const EcParams& e, int cnt, const float* u_lds, float* hid,
                              float* v_tile) {
   const int tid = threadIdx.x, nthr = blockDim.x;
   const int r = e.r;
   if (e.gate == GATE_TANH) {
-    for (int t = 0; t < cnt; ++t) {
-      const float* u = u_lds + t * e.R1p;
-      for (int i = tid; i < e.h; i += nthr) {
-        float a = act2f<DT>(e.b1[i]);
-        const uint16_t* w1 = e.W1 + (size_t)i * r;
-        for (int j = 0; j < r; ++j) a += act2f<DT>(w1[j]) * u[j];
-        hid[i] = a > 0.f ? a : 0.f;
-      }
-      __syncthreads();
-      for (int j = tid; j < r; j += nthr) {
-        float a = act2f<DT>(e.b2[j]);
-        const uint16_t* w2 = e.W2 + (size_t)j * e.h;
-        for (int i = 0; i < e.h; ++i) a += act2f<DT>(w2[i]) * hid[i];
-        v_tile[t * r + j] = e.alpha * (1.f + tanhf(a)) * u[j];
-      }
-      __syncthreads();
-    }
+    tanh_gate_tokens<DT>(cnt, r, e.h, u_lds, e.R1p, e.W1, e.b1, e.W2, e.b2, e.alpha, hid,
+                         ec_hid_tokens(e.h), v_tile, r);
   } else {
     for (int idx = tid; idx < cnt * r; idx += nthr) {
       const int t = idx / r, j = idx - t * r;
@@ -199,7 +184,7 @@ __device__ __forceinline__ void ec_producer(const EcParams& e, int b, uint32_t g
   char* es = smem + ec_red_bytes(NW);
   float* u_lds = (float*)(es + ec_lds_u_off());
   float* hid = (float*)(es + ec_lds_hid_off(e.R1p));
-  float* v_tile = (float*)(es + ec_lds_v_off(e.R1p, e.h));
+  float* v_tile = (float*)(es + ec_lds_v_off(e.R1p, ec_hid_floats(e.h)));
   const int m0 = tb * kTokTile;
   const int cnt = min(kTokTile, e.M - m0);
   const int j_beg = 16 * t_beg, nj = min(e.R1, 16 * t_end) - j_beg;
@@ -298,7 +283,7 @@ __global__ __launch_bounds__(256) void k_gate(EcParams e) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   float* u_lds = (float*)(smem + ec_lds_u_off());
   float* hid = (float*)(smem + ec_lds_hid_off(e.R1p));
-  float* v_tile = (float*)(smem + ec_lds_v_off(e.R1p, e.h));
+  float* v_tile = (float*)(smem + ec_lds_v_off(e.R1p, ec_hid_floats(e.h)));
   const int m0 = blockIdx.x * kTokTile;
   const int cnt = min(kTokTile, e.M - m0);
   for (int idx = threadIdx.x; idx < cnt * e.R1; idx += blockDim.x) {
@@ -1293,13 +1278,9 @@ __device__ __forceinline__ void gemv_body(const GemvParams& a, int bid, uint32_t
   // gate row's sum plus b_g, or one; or the tanh-MLP gate of u, whose hidden
   // layer takes the LDS after v), then y += v B^T in fp32 below
   if (kLoc && !v_direct && a.ec.gate == GATE_TANH) {
-    // LDS after v: the hidden layer (cap x h floats), then the staged
-    // parameters when they fit
-    float* hid = v_loc + 16 * MT * r;
-    const int cap = local_tanh_cap(M, a.ec.h);
-    uint16_t* wst = tanh_stage_halves(a.ec.h, r) > 0 ? (uint16_t*)(hid + cap * a.ec.h) : nullptr;
+    // LDS after v: the hidden layer (cap x h floats)
     tanh_gate_tokens<DT>(M, r, a.ec.h, u_loc, R1p, a.ec.W1, a.ec.b1, a.ec.W2, a.ec.b2, a.ec.alpha,
-                         hid, cap, v_loc, r, wst);
+                         v_loc + 16 * MT * r, local_tanh_cap(M, a.ec.h), v_loc, r);
   } else if (kLoc && !v_direct) {
     for (int idx = tid; idx < M * r; idx += blockDim.x) {
       const int m = idx / r, j = idx - m * r;

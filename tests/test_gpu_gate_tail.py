@@ -1,13 +1,15 @@
-"""GPU parity of the row lengths of the post-EC tail's RMSNorm against float64."""
+"""GPU parity of the row lengths of the post-EC tail's RMSNorm and of the token
+counts and widths of the tanh-MLP gate, against the float64 oracle."""
 from __future__ import annotations
 
 import numpy as np
 import pytest
 import torch
 
+from oracle import spear_oracle as O
 from paper_2606_11244_amd import synth as S
 
-from gpu_util import log
+from gpu_util import assert_parity, gpu_y, log, scaled_ec, zero_weight
 
 pytestmark = pytest.mark.gpu
 
@@ -46,3 +48,23 @@ def test_rmsnorm_row_lengths(N, dt):
     ulp = 2.0 ** (-11 if dt == S.F16 else -8)
     got = yn.float().cpu().numpy().astype(np.float64)
     assert np.all(np.abs(got - ref) <= 1.01 * ulp * np.abs(ref) + 1e-7), np.abs(got - ref).max()
+
+
+# (M, rank, hidden, path): token groups of four and their remainders, ranks and
+# hidden widths with and without whole 16-byte parameter rows, the largest
+# hidden width (four tokens at once), one producer and several
+TANH = [(1, 8, 0, 4), (5, 12, 20, 4), (16, 32, 128, 4), (17, 33, 40, 4), (40, 64, 256, 4),
+        (3, 16, 1024, 4), (130, 20, 72, 4), (1, 32, 128, 1), (9, 64, 256, 1), (4, 24, 1000, 1),
+        (6, 16, 64, 5), (31, 12, 30, 5), (2, 5, 17, 5), (50, 16, 64, 2), (140, 9, 33, 2), (7, 32, 96, 3)]
+
+
+@pytest.mark.parametrize("M,rank,h,path", TANH)
+@pytest.mark.parametrize("dt", [S.F16, S.BF16])
+def test_tanh_gate_shapes(M, rank, h, path, dt):
+    """The EC term alone (zero weight, EC x 30), so that the bar applies to the
+    gate and not to the product that hides it."""
+    L = S.make_layer(M=M, N=80, K=512, group_size=128, rank=rank, act_dtype=dt,
+                     gate_kind=S.GATE_TANH_MLP, gate_hidden=h, seed=M * 7 + rank)
+    L = scaled_ec(zero_weight(L), 30)
+    log(f"tanh M={M} r={rank} h={h} path={path} dt={dt}")
+    assert_parity(gpu_y(L, path=path), O.w4ec_linear(L), f"tanh path={path}")
