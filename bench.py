@@ -73,7 +73,7 @@ def algo_flops(M, N, K, r):
 
 def kernel_source_hash() -> str:
     h = hashlib.sha256()
-    for f in ("spear_kernels.hip", "spear_gemm.hip", "spear_device.h", "spear_api.cpp", "spear_internal.h"):
+    for f in ("spear_kernels.hip", "spear_gemm.hip", "spear_mid.hip", "spear_device.h", "spear_api.cpp", "spear_internal.h"):
         with open(os.path.join(ROOT, "paper_2606_11244_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]

@@ -30,7 +30,7 @@ COMMON = ["-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
 # the kernel files compile once per code width (SPEAR_WB) and activation dtype
 UNITS = tuple((src, f"w{wb}_{'bf16' if bf else 'f16'}",
                [f"--offload-arch={ARCH}", "-x", "hip", f"-DSPEAR_WB={wb}", f"-DSPEAR_BF16_UNIT={bf}"])
-              for src in ("spear_kernels.hip", "spear_gemm.hip") for wb in (4, 3) for bf in (0, 1)) + (
+              for src in ("spear_kernels.hip", "spear_gemm.hip", "spear_mid.hip") for wb in (4, 3) for bf in (0, 1)) + (
     ("spear_api.cpp", "", [f"--offload-arch={ARCH}", "-x", "hip"]),
     ("spear_sched.cpp", "", [f"--offload-arch={ARCH}"]))
 

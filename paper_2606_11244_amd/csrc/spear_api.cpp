@@ -51,7 +51,9 @@ struct Resolved {
   int nst;                                    // GEMV stages of codes in flight per wave
   int Sg;                                     // GEMM K-slices
   int gtmw;                                   // GEMM token waves (2: 128-token tiles, 4: 256)
-  int groles;                                 // GEMM wave roles (1: every wave both, 2, 3: split)
+  int groles;                                 // GEMM wave roles (1: every wave both, 2, 3: split,
+                                              // 4: k_gemm_r)
+  int gmid, gips;                             // k_gemm_r: token tiles, iterations per K-slice
   int ntb, P, eips, PG, tpg, ec_mode, ec_ipp, ec_block, n_prod;  // EC shape
   int xlds, xstride, bpre, lds_y, lds_e, lds_b, lds_g, lds_ev, lds_sz, lds_a;
   size_t off_vtag, off_upart, off_v, off_vh, off_vl, off_u, off_ypart, off_eupart, off_gpart,
@@ -147,6 +149,39 @@ int gemv_rt(int MT, int kind, int64_t N, int IT, int NW, int rt_force, int waves
   return MT <= 2 && !(kind == kRtLocal && MT == 2) ? 2 : 1;
 }
 
+// k_gemm_r's shape: as few token tiles of at most 128 tokens as cover M, each
+// as narrow as that allows, and K-slices of at least four iterations until
+// the grid has 160 workgroups (a second slice on a grid that already fills
+// most of the CUs costs more in partial tiles than it fills: 70B gate at 64
+// tokens, 224 tiles: 64 us unsplit, 72 in two slices; q, 64 tiles: 50 us
+// unsplit, 35 in two, 24 in four). MT 0: the slices' scales exceed the LDS.
+struct MidShape {
+  int MT = 0, S = 0, ips = 0;
+};
+MidShape mid_shape(int64_t M, int64_t N, int IT, int G, int ngroups) {
+  MidShape m;
+  const int64_t tms = cdiv(M, 128);
+  for (int mt : {2, 3, 4, 6, 8})
+    if (m.MT == 0 && 16 * mt * tms >= M) m.MT = mt;
+  if (m.MT == 0) return m;
+  const int ipg = G / kIterK;
+  auto fits = [&](int S) {  // no empty slice, and the slice's scales fit
+    const int ips = (int)cdiv(IT, S);
+    return (S - 1) * ips < IT && mid_lds(m.MT, std::min(ngroups, (int)cdiv(ips, ipg) + 1)) <= kMaxLds;
+  };
+  const int64_t wgs = mid_tiles(m.MT, (int)M, (int)N);
+  if (g_ov_gs.load() > 0) {
+    m.S = g_ov_gs.load();
+    if ((m.S != 1 && m.S != 2 && m.S != 4 && m.S != 8) || !fits(m.S)) m.MT = 0;
+  } else {
+    for (int S = 1; S <= 8; S *= 2)
+      if ((m.S == 0 || (wgs * m.S < 160 && IT / S >= 4)) && fits(S)) m.S = S;
+    if (m.S == 0 || wgs * m.S > kMaxRowCounters) m.MT = 0;
+  }
+  if (m.MT > 0) m.ips = (int)cdiv(IT, m.S);
+  return m;
+}
+
 spear_status_t resolve(const spear_problem_t* p, bool with_ec, Resolved* R, int rt_force = 0) {
   spear_status_t st = validate_shape(p, with_ec);
   if (st != SPEAR_OK) return st;
@@ -224,12 +259,24 @@ spear_status_t resolve(const spear_problem_t* p, bool with_ec, Resolved* R, int 
   // rank 16: 11.2 us against 13.3 us)
   const bool narrow_deep1 = M == 1 && N < kFusedNarrowN && K >= 8192 &&
                             K / kIterK <= (kGemvMaxThreads / 64 - 1) * kFusedCapIw;
+  // k_gemm_r, the GEMM that keeps the codes in registers, for the 4-bit
+  // product and the semi-fused pair. 33 to 128 tokens: MID_RULE
+  // At 17 to 32 tokens, where it does not round the weights either: MID_RULE32
+  const MidShape ms = M > kTokTile && N > 0 ? mid_shape(M, N, z.IT, z.G, z.ngroups) : MidShape();
+  const bool mid_fits = ms.MT > 0 && g_ov_gt.load() == 0;
+  int sg = 1;  // k_gemm's K-slices (below): an even number of 64-wide steps each
+  for (int S = 2; S <= 8; S *= 2)
+    if (cdiv(N, kGemmTN) * sg < 256 && K / kGemmTK % (2 * S) == 0 && K / kGemmTK / S >= 4) sg = S;
+  const bool mid_pays = M <= 96 || (M <= 128 && (N * K >= ((int64_t)1 << 25) || cdiv(N, kGemmTN) * sg < 128));
+  const bool mid = mid_fits && (g_ov_gr.load() == 4 ||
+                                (g_ov_gr.load() == 0 && mid_pays &&
+                                 (M > kAutoGemvMaxM || N < 8192 || K < 8192 || z.ec)));
   if (path == SPEAR_PATH_AUTO || !z.ec)
     path = M > kAutoGemvMaxM ? (mfma_ok && few_tiles && !big_tiles ? SPEAR_PATH_FUSED_MFMA
                                                                    : SPEAR_PATH_UNFUSED_2K)
            : local_ok && !narrow_deep1 ? SPEAR_PATH_FUSED_LOCAL
-           : deep1           ? SPEAR_PATH_UNFUSED_2K
-                             : SPEAR_PATH_FUSED_GEMV;
+           : deep1 || (mid && (z.r <= 16 || (N < 8192 && K > 8192))) ? SPEAR_PATH_UNFUSED_2K
+                                                                     : SPEAR_PATH_FUSED_GEMV;
   if (!with_ec) {
     // the 4-bit product alone: the GEMV up to kAutoGemvMaxM tokens, the
     // GEMM above; force_path picks the kernel (GEMV paths: the GEMV, up to
@@ -246,9 +293,10 @@ spear_status_t resolve(const spear_problem_t* p, bool with_ec, Resolved* R, int 
   const bool fmfma = z.ec && path == SPEAR_PATH_FUSED_MFMA;
   // the GEMV for the GEMV paths, and under the 4-bit product of the
   // two-kernel and chain paths up to kAutoGemvMaxM tokens (the GEMM above)
-  z.gemv = !with_ec ? path == SPEAR_PATH_FUSED_GEMV
+  z.gemv = !with_ec ? path == SPEAR_PATH_FUSED_GEMV &&
+                          !(mid && p->force_path != SPEAR_PATH_FUSED_GEMV && p->force_path != SPEAR_PATH_FUSED_LOCAL)
            : path == SPEAR_PATH_FUSED_GEMV || path == SPEAR_PATH_FUSED_LOCAL ||
-                 (!fmfma && M <= kAutoGemvMaxM);
+                 (!fmfma && M <= kAutoGemvMaxM && !mid);
   z.plan.path = path;
 
   if (M == 0 || N == 0) {
@@ -377,7 +425,7 @@ spear_status_t resolve(const spear_problem_t* p, bool with_ec, Resolved* R, int 
       if (tiles * z.Sg < 256 && steps % (2 * S) == 0 && steps / S >= 4) z.Sg = S;
     if (g_ov_gs.load() > 0) {
       const int S = g_ov_gs.load();
-      if (steps % (2 * S) != 0) return SPEAR_E_UNSUPPORTED;
+      if (steps % (2 * S) != 0 && !(mid && !fmfma)) return SPEAR_E_UNSUPPORTED;
       z.Sg = S;
     }
     // 256-token tiles in one K-slice (the plain and the semi-fused
@@ -385,12 +433,19 @@ spear_status_t resolve(const spear_problem_t* p, bool with_ec, Resolved* R, int 
     // tiles while those alone fill the 256 CUs, else 256 x 128
     const bool split_ok = z.gtmw == 4 && z.Sg == 1;
     z.groles = !split_ok ? 1 : cdiv(M, tm) * cdiv(N, 2 * kGemmTN) >= 256 ? 3 : 2;
-    if (g_ov_gr.load() > 0) {
+    if (g_ov_gr.load() > 0 && g_ov_gr.load() != 4) {
       z.groles = g_ov_gr.load();
       if (z.groles >= 2 && !split_ok) return SPEAR_E_UNSUPPORTED;
     }
+    if (g_ov_gr.load() == 4 && (fmfma || !mid)) return SPEAR_E_UNSUPPORTED;
+    if (!fmfma && mid) {
+      z.groles = 4;
+      z.gmid = ms.MT;
+      z.Sg = ms.S;
+      z.gips = ms.ips;
+    }
     z.plan.split_k = z.Sg;
-    z.plan.tile_m = tm;
+    z.plan.tile_m = z.groles == 4 ? 128 : tm;  // k_gemm_r: at most (gmid token tiles of 16)
     z.plan.tile_n = z.groles == 3 ? 2 * kGemmTN : kGemmTN;
   }
 
@@ -507,7 +562,9 @@ spear_status_t resolve(const spear_problem_t* p, bool with_ec, Resolved* R, int 
   z.plan.ec_splits = z.ec ? z.P : 0;
 
   // launches and grid
-  const int grid4 = z.gemv ? z.nrg * z.S : (int)(cdiv(M, z.plan.tile_m) * cdiv(N, z.plan.tile_n)) * z.Sg;
+  const int grid4 = z.gemv          ? z.nrg * z.S
+                    : z.groles == 4 ? mid_tiles(z.gmid, (int)M, (int)N) * z.Sg
+                                    : (int)(cdiv(M, z.plan.tile_m) * cdiv(N, z.plan.tile_n)) * z.Sg;
   if (!z.ec || local || fmfma) {
     z.plan.num_launches = 1;
     z.plan.grid = grid4;
@@ -573,8 +630,9 @@ spear_status_t resolve(const spear_problem_t* p, bool with_ec, Resolved* R, int 
     z.off_ypart = take((size_t)z.S * M * N * 4);
   }
   if (!z.gemv && z.Sg > 1) {
-    const int64_t tiles = cdiv(M, z.plan.tile_m) * cdiv(N, kGemmTN);
-    const size_t part = (size_t)z.Sg * tiles * z.plan.tile_m * kGemmTN * 4;
+    const int tok = z.groles == 4 ? 16 * z.gmid : z.plan.tile_m;
+    const int64_t tiles = cdiv(M, tok) * cdiv(N, kGemmTN);
+    const size_t part = (size_t)z.Sg * tiles * tok * kGemmTN * 4;
     // the kernel addresses the partial tiles with 32-bit offsets
     if (tiles > kMaxRowCounters || part >= ((size_t)1 << 31)) return SPEAR_E_SHAPE;
     z.off_gpart = take(part);
@@ -734,6 +792,7 @@ GemmParams make_gemm(const spear_problem_t* p, const Resolved& z, const void* x,
   g.S = std::max(1, z.Sg);
   g.tmw = z.gtmw ? z.gtmw : 2;
   g.roles = z.groles >= 2 ? z.groles : 1;
+  g.ips = z.gips;
   if (ws && z.Sg > 1) {
     g.ypart = (float*)(ws + z.off_gpart);
     g.ctr = (uint32_t*)(ws + kCtrRows);
@@ -819,7 +878,25 @@ hipError_t launch_gemv_wb(const Resolved& z, int epi, const GemvParams& p, int g
   return SPEAR_BY_WB(launch_gemv, z.wb, z.dt)(z.MT, z.RT, epi, nst, p, grid, block, lds, st);
 }
 hipError_t launch_gemm_wb(const Resolved& z, int epi, const GemmParams& p, hipStream_t st) {
+  if (z.groles == 4) {
+    GemmGroup g;
+    std::memset(&g, 0, sizeof(g));
+    g.p[0] = p;
+    g.start[1] = mid_tiles(z.gmid, p.M, p.N) * p.S;
+    g.n = 1;
+    return SPEAR_BY_WB(launch_mid, z.wb, z.dt)(z.gmid, g, st);
+  }
   return SPEAR_BY_WB(launch_gemm, z.wb, z.dt)(epi, p, st);
+}
+
+// the EC pre-kernel of one layer
+spear_status_t run_ec(const Resolved& z, const EcParams& e, hipStream_t st) {
+  EcGroup g;
+  std::memset(&g, 0, sizeof(g));
+  g.p[0] = e;
+  g.start[1] = z.ntb * z.P * z.PG;
+  g.n = 1;
+  return hip_status(SPEAR_BY_DT(launch_ec, z.dt)(g, z.ec_block, z.ec_ipp, z.lds_prod, st));
 }
 
 // res: [M][N] act-dtype residual added before the output's single rounding, or null
@@ -835,6 +912,36 @@ spear_status_t run_w4(const spear_problem_t* p, const Resolved& z, const void* x
   return hip_status(launch_gemm_wb(z, EPI_NONE, g, st));
 }
 
+// The semi-fused path: the EC pre-kernel's parameters, and the 4-bit product
+// with the epilogue that adds its result (its counters lie at `base`, the
+// workspace itself where `ws` is a member's part of a group's).
+EcParams ec_for_2k(const spear_problem_t* prob, const Resolved& z, const void* x, const spear_ec_t* ec,
+                   char* ws) {
+  EcParams e = make_ec(prob, z, x, ec, ws);
+  if (!z.gemv) {
+    e.vh = (uint16_t*)(ws + z.off_vh);
+    e.vl = (uint16_t*)(ws + z.off_vl);
+    e.v = nullptr;
+  }
+  return e;
+}
+spear_status_t run_2k_main(const spear_problem_t* prob, const Resolved& z, const void* x,
+                           const spear_w4_t* w, const spear_ec_t* ec, const EcParams& e, void* y,
+                           const uint16_t* res, char* ws, hipStream_t s, char* base = nullptr) {
+  if (!base) base = ws;
+  if (z.gemv) {
+    GemvParams g = make_gemv(prob, z, x, w, y, ec, ws);
+    if (z.S > 1) g.rb_ctr = (uint32_t*)(base + kCtrRows);
+    g.res = res;
+    g.ec = e;
+    return hip_status(launch_gemv_wb(z, EPI_READY, g, z.nrg * z.S, 64 * (z.NW + 1), z.lds_gemv, s));
+  }
+  GemmParams g = make_gemm(prob, z, x, w, y, ec, ws);
+  if (z.Sg > 1) g.ctr = (uint32_t*)(base + kCtrRows);
+  g.res = res;
+  return hip_status(launch_gemm_wb(z, EPI_READY, g, s));
+}
+
 // The layer on its planned path, after validation; res as in run_w4 (the
 // chain adds it in its 4-bit kernel, every other path in its final store).
 spear_status_t run_layer(const spear_problem_t* prob, const Resolved& z, const void* x,
@@ -845,7 +952,6 @@ spear_status_t run_layer(const spear_problem_t* prob, const Resolved& z, const v
 
   EcParams e = make_ec(prob, z, x, ec, ws);
   const int path = z.plan.path;
-  const int ec_grid = z.ntb * z.P * z.PG;
   if (path == SPEAR_PATH_FUSED_MFMA) {
     GemmParams g = make_gemm(prob, z, x, w, y, ec, ws);
     g.res = res;
@@ -875,23 +981,9 @@ spear_status_t run_layer(const spear_problem_t* prob, const Resolved& z, const v
     return hip_status(launch_gemv_wb(z, EPI_FUSED, g, g.grid_total, 64 * (z.NW + 1), lds, s));
   }
   if (path == SPEAR_PATH_UNFUSED_2K) {
-    if (!z.gemv) {
-      e.vh = (uint16_t*)(ws + z.off_vh);
-      e.vl = (uint16_t*)(ws + z.off_vl);
-      e.v = nullptr;
-    }
-    st = hip_status(SPEAR_BY_DT(launch_ec, z.dt)(e, ec_grid, z.ec_block, z.ec_ipp, z.lds_prod, s));
-    if (st != SPEAR_OK) return st;
-    if (z.gemv) {
-      GemvParams g = make_gemv(prob, z, x, w, y, ec, ws);
-      g.res = res;
-      g.ec = e;
-      return hip_status(launch_gemv_wb(z, EPI_READY, g, z.nrg * z.S, 64 * (z.NW + 1), z.lds_gemv,
-                                       s));
-    }
-    GemmParams g = make_gemm(prob, z, x, w, y, ec, ws);
-    g.res = res;
-    return hip_status(launch_gemm_wb(z, EPI_READY, g, s));
+    e = ec_for_2k(prob, z, x, ec, ws);
+    st = run_ec(z, e, s);
+    return st != SPEAR_OK ? st : run_2k_main(prob, z, x, w, ec, e, y, res, ws, s);
   }
   if (path == SPEAR_PATH_OVERLAP_2K) {
     // fork: the EC pre-kernel (A x, gate, v in fp32) on the side stream,
@@ -902,7 +994,7 @@ spear_status_t run_layer(const spear_problem_t* prob, const Resolved& z, const v
     if ((st = side_stream(&ss)) != SPEAR_OK) return st;
     if (hipEventRecord(ss->fork, s) != hipSuccess || hipStreamWaitEvent(ss->s, ss->fork, 0) != hipSuccess)
       return SPEAR_E_HIP;
-    st = hip_status(SPEAR_BY_DT(launch_ec, z.dt)(e, ec_grid, z.ec_block, z.ec_ipp, z.lds_prod, ss->s));
+    st = run_ec(z, e, ss->s);
     if (st != SPEAR_OK) return st;
     if (hipEventRecord(ss->join, ss->s) != hipSuccess) return SPEAR_E_HIP;
     st = run_w4(prob, z, x, w, y, ws, s, res);
@@ -918,7 +1010,7 @@ spear_status_t run_layer(const spear_problem_t* prob, const Resolved& z, const v
   st = run_w4(prob, z, x, w, y, ws, s, res);
   if (st != SPEAR_OK) return st;
   e.u_out = (float*)(ws + z.off_u);
-  st = hip_status(SPEAR_BY_DT(launch_ec, z.dt)(e, ec_grid, z.ec_block, z.ec_ipp, z.lds_prod, s));
+  st = run_ec(z, e, s);
   if (st != SPEAR_OK) return st;
   st = hip_status(SPEAR_BY_DT(launch_gate, z.dt)(e, z.ntb, z.lds_gate, s));
   if (st != SPEAR_OK) return st;
@@ -1185,6 +1277,43 @@ int group_select(int32_t n, const spear_layer_call_t* calls, Resolved* z, bool* 
   return n_in;
 }
 
+// The members outside the shared GEMV launch that share a launch with others:
+// set[i], the first member of i's shared k_gemm_r launch, or -1, and
+// ec_set[i], the same for its EC pre-kernel (semi-fused members; each runs
+// its 4-bit product on its own where set[i] is -1). Sets have at least two
+// members. They run exactly the workgroups of their own launches.
+void prefill_sets(int32_t n, const spear_layer_call_t* calls, const Resolved* z, const bool* in, int* set,
+                  int* ec_set) {
+  int key[SPEAR_GROUP_MAX], ekey[SPEAR_GROUP_MAX];
+  for (int i = 0; i < n; ++i) {
+    const bool live = !in[i] && calls[i].prob->M > 0 && calls[i].prob->N > 0;
+    const bool two = live && z[i].ec && z[i].plan.path == SPEAR_PATH_UNFUSED_2K;
+    const bool w4 = live && !z[i].ec;
+    key[i] = (two || w4) && !z[i].gemv && z[i].groles == 4 ? (z[i].gmid * 2 + z[i].dt) * 8 + z[i].wb : -1;
+    ekey[i] = two ? (z[i].ec_block * 4 + z[i].ec_ipp) * 2 + z[i].dt : -1;
+  }
+  auto collect = [&](const int* k, int* out, int max_ctr, auto ctrs) {
+    for (int i = 0; i < n; ++i) out[i] = -1;
+    for (int i = 0; i < n; ++i) {
+      if (k[i] < 0 || out[i] >= 0) continue;
+      int cnt = 0, sum = 0;
+      for (int j = i; j < n; ++j)
+        if (k[j] == k[i]) ++cnt, sum += ctrs(j);
+      if (cnt < 2 || sum > max_ctr) continue;
+      for (int j = i; j < n; ++j)
+        if (k[j] == k[i]) out[j] = i;
+    }
+  };
+  collect(key, set, kMaxRowCounters, [&](int j) {
+    return z[j].Sg > 1 ? mid_tiles(z[j].gmid, (int)calls[j].prob->M, (int)calls[j].prob->N) : 0;
+  });
+  collect(ekey, ec_set, kMaxEcCounters, [&](int j) { return z[j].ntb; });
+  // a semi-fused member's EC result must be in its own part of the workspace
+  // when its 4-bit product shares a launch: it then takes the shared EC path
+  for (int i = 0; i < n; ++i)
+    if (set[i] >= 0 && z[i].ec && ec_set[i] < 0) ec_set[i] = i;
+}
+
 spear_status_t spear_group_workspace(int32_t n, const spear_layer_call_t* calls, size_t* out_bytes) {
   Resolved z[SPEAR_GROUP_MAX];
   size_t off[SPEAR_GROUP_MAX];
@@ -1200,9 +1329,18 @@ spear_status_t spear_group_launches(int32_t n, const spear_layer_call_t* calls, 
   bool in[SPEAR_GROUP_MAX];
   int epi = -1, first = -1;
   const int n_in = group_select(n, calls, z, in, &epi, &first);
+  int set[SPEAR_GROUP_MAX], ec_set[SPEAR_GROUP_MAX];
+  prefill_sets(n, calls, z, in, set, ec_set);
+  // one launch per shared set (counted at its first member)
   int32_t launches = n_in > 0 ? 1 : 0;
-  for (int i = 0; i < n; ++i)
-    if (!in[i] && calls[i].prob->M > 0 && calls[i].prob->N > 0) launches += z[i].plan.num_launches;
+  for (int i = 0; i < n; ++i) {
+    if (in[i] || calls[i].prob->M == 0 || calls[i].prob->N == 0) continue;
+    const int ec_launch = ec_set[i] < 0 ? 0 : ec_set[i] == i ? 1 : 0;
+    const int main_launch = set[i] < 0 ? 1 : set[i] == i ? 1 : 0;
+    launches += ec_set[i] >= 0 ? ec_launch + main_launch
+                : set[i] >= 0  ? main_launch
+                               : z[i].plan.num_launches;
+  }
   *out_launches = launches;
   return SPEAR_OK;
 }
@@ -1244,10 +1382,63 @@ spear_status_t spear_w4ec_linear_group(int32_t n, const spear_layer_call_t* call
   bool in[SPEAR_GROUP_MAX];
   int epi = -1, first = -1;
   const int n_in = group_select(n, calls, z, in, &epi, &first);
+  int set[SPEAR_GROUP_MAX], ec_set[SPEAR_GROUP_MAX];
+  prefill_sets(n, calls, z, in, set, ec_set);
+  // members that share nothing: each as its own call would run, in the
+  // workspace a single call would use
   for (int i = 0; i < n; ++i) {
     const spear_layer_call_t& c = calls[i];
-    if (in[i] || c.prob->M == 0 || c.prob->N == 0) continue;
+    if (in[i] || set[i] >= 0 || ec_set[i] >= 0 || c.prob->M == 0 || c.prob->N == 0) continue;
     st = run_layer(c.prob, z[i], c.x, c.w, c.ec, c.y, nullptr, ws, s);
+    if (st != SPEAR_OK) return st;
+  }
+  // the shared EC pre-kernels, then the 4-bit products that add their
+  // results, each set in one launch: every member's data in its own part of
+  // the workspace, its counters after the earlier members'
+  EcParams ecp[SPEAR_GROUP_MAX];
+  for (int k = 0; k < n; ++k) {
+    if (ec_set[k] != k) continue;
+    EcGroup g;
+    std::memset(&g, 0, sizeof(g));
+    size_t lds = 0;
+    int ctr = 0;
+    for (int i = k; i < n; ++i) {
+      if (ec_set[i] != k) continue;
+      ecp[i] = ec_for_2k(calls[i].prob, z[i], calls[i].x, calls[i].ec, ws + off[i]);
+      ecp[i].ctr = (uint32_t*)(ws + kCtrEc) + ctr;
+      ctr += z[i].ntb;
+      g.p[g.n] = ecp[i];
+      g.start[g.n + 1] = g.start[g.n] + z[i].ntb * z[i].P * z[i].PG;
+      lds = std::max(lds, z[i].lds_prod);
+      ++g.n;
+    }
+    st = hip_status(SPEAR_BY_DT(launch_ec, z[k].dt)(g, z[k].ec_block, z[k].ec_ipp, lds, s));
+    if (st != SPEAR_OK) return st;
+  }
+  for (int k = 0; k < n; ++k) {
+    const spear_layer_call_t& c = calls[k];
+    if (set[k] < 0 && ec_set[k] >= 0) {
+      st = run_2k_main(c.prob, z[k], c.x, c.w, c.ec, ecp[k], c.y, nullptr, ws + off[k], s, ws);
+      if (st != SPEAR_OK) return st;
+    }
+    if (set[k] != k) continue;
+    GemmGroup g;
+    std::memset(&g, 0, sizeof(g));
+    int ctr = 0;
+    for (int i = k; i < n; ++i) {
+      if (set[i] != k) continue;
+      const spear_layer_call_t& m = calls[i];
+      GemmParams& q = g.p[g.n];
+      q = make_gemm(m.prob, z[i], m.x, m.w, m.y, z[i].ec ? m.ec : nullptr, ws ? ws + off[i] : nullptr);
+      const int tiles = mid_tiles(z[i].gmid, (int)m.prob->M, (int)m.prob->N);
+      if (z[i].Sg > 1) {
+        q.ctr = (uint32_t*)(ws + kCtrRows) + ctr;
+        ctr += tiles;
+      }
+      g.start[g.n + 1] = g.start[g.n] + tiles * z[i].Sg;
+      ++g.n;
+    }
+    st = hip_status(SPEAR_BY_WB(launch_mid, z[k].wb, z[k].dt)(z[k].gmid, g, s));
     if (st != SPEAR_OK) return st;
   }
   if (n_in == 0) return SPEAR_OK;
@@ -1357,7 +1548,7 @@ void spear_set_gemm_slices(int32_t k_slices) { g_ov_gs = k_slices > 0 ? k_slices
 void spear_set_gemv_stages(int32_t stages) { g_ov_nst = stages > 0 ? stages : 0; }
 
 void spear_set_gemm_tile(int32_t tokens) { g_ov_gt = tokens == 128 || tokens == 256 ? tokens : 0; }
-void spear_set_gemm_roles(int32_t roles) { g_ov_gr = roles >= 1 && roles <= 3 ? roles : 0; }
+void spear_set_gemm_roles(int32_t roles) { g_ov_gr = roles >= 1 && roles <= 4 ? roles : 0; }
 
 const char* spear_status_string(spear_status_t s) {
   switch (s) {

@@ -1,4 +1,5 @@
-// Device helpers shared by the kernel files (spear_kernels.hip, spear_gemm.hip):
+// Device helpers shared by the kernel files (spear_kernels.hip, spear_gemm.hip,
+// spear_mid.hip):
 // MFMA wrappers, code unpacking, bounds-checked buffer accesses, coherent
 // cross-workgroup reads.
 //
@@ -93,6 +94,13 @@ __device__ __forceinline__ uint16_t f2act(float f) {
     return __builtin_bit_cast(uint16_t, (_Float16)f);
   else
     return __builtin_bit_cast(uint16_t, (__bf16)f);
+}
+
+// two fp32 values, rounded to nearest even, as a bf16 pair (one instruction)
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{a, b}, bf16x2));
 }
 
 __device__ __forceinline__ float h2f(uint16_t b) { return (float)__builtin_bit_cast(_Float16, b); }
@@ -314,26 +322,8 @@ __device__ __forceinline__ u32x2 bld64c(rsrc_t r, uint32_t off) {
   return __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0x10);
 }
 
-// dst[i] = fp32 word at byte offset off(i) of `r`, i in [0, n). (Four named
-// registers rather than an array: the loads must stay out of scratch.)
-template <class Off>
-__device__ __forceinline__ void gather_f32(rsrc_t r, int n, Off off, float* dst) {
-  const int nthr = blockDim.x;
-  for (int i0 = threadIdx.x; i0 < n; i0 += 4 * nthr) {
-    const int i1 = i0 + nthr, i2 = i1 + nthr, i3 = i2 + nthr;
-    const uint32_t w0 = bld32c(r, off(i0));
-    const uint32_t w1 = bld32c(r, i1 < n ? off(i1) : kOOB);
-    const uint32_t w2 = bld32c(r, i2 < n ? off(i2) : kOOB);
-    const uint32_t w3 = bld32c(r, i3 < n ? off(i3) : kOOB);
-    dst[i0] = __uint_as_float(w0);
-    if (i1 < n) dst[i1] = __uint_as_float(w1);
-    if (i2 < n) dst[i2] = __uint_as_float(w2);
-    if (i3 < n) dst[i3] = __uint_as_float(w3);
-  }
-}
-
-// Same for tagged words (tag << 32 | fp32 bits); returns 1 if any word this
-// thread read carries another tag.
+// dst[i] = fp32 part of the tagged word (tag << 32 | fp32 bits) at off(i), i in
+// [0, n); returns 1 if any word this thread read carries another tag.
 template <class Off>
 __device__ __forceinline__ int gather_tagged(rsrc_t r, int n, Off off, uint32_t tag, float* dst) {
   const int nthr = blockDim.x;
@@ -354,25 +344,37 @@ __device__ __forceinline__ int gather_tagged(rsrc_t r, int n, Off off, uint32_t 
 }
 
 // out(i, sum over q < P of the word at off(q, i)), i in [0, n), summed in
-// slice order; the words go through `scratch` (cap floats of LDS) in chunks.
-// Every thread of the block calls it; it ends with a barrier.
+// slice order. The slices lie at the device coherence point, a memory round
+// trip away, so each thread sums two elements at a time with eight slices of
+// both in flight and nothing goes through LDS (a staged copy of bounded size
+// took six dependent round trips for a 16-token tile of rank 64 in eight
+// slices: EC_SUM_MEASURED). Every thread of the block calls it; it ends with a
+// barrier.
 template <class Off, class Out>
-__device__ void sum_slices(rsrc_t r, int P, int n, Off off, float* scratch, int cap, Out out) {
-  const int C = max(1, cap / P);
-  for (int e0 = 0; e0 < n; e0 += C) {
-    const int c = min(C, n - e0);
-    gather_f32(r, P * c, [&](int i) {
-      const int q = i / c;
-      return off(q, e0 + (i - q * c));
-    }, scratch);
-    __syncthreads();
-    for (int i = threadIdx.x; i < c; i += blockDim.x) {
-      float v = 0.f;
-      for (int q = 0; q < P; ++q) v += scratch[q * c + i];
-      out(e0 + i, v);
+__device__ __forceinline__ void sum_slices(rsrc_t r, int P, int n, Off off, Out out) {
+  const int nthr = blockDim.x;
+  for (int i0 = threadIdx.x; i0 < n; i0 += 2 * nthr) {
+    const int i1 = i0 + nthr;
+    float a = 0.f, b = 0.f;
+    for (int q0 = 0; q0 < P; q0 += 8) {
+      uint32_t wa[8], wb[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const bool ok = q0 + u < P;
+        wa[u] = bld32c(r, ok ? off(q0 + u, i0) : kOOB);
+        wb[u] = bld32c(r, ok && i1 < n ? off(q0 + u, i1) : kOOB);
+      }
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        if (q0 + u < P) {
+          a += __uint_as_float(wa[u]);
+          b += __uint_as_float(wb[u]);
+        }
     }
-    __syncthreads();
+    out(i0, a);
+    if (i1 < n) out(i1, b);
   }
+  __syncthreads();
 }
 
 // One layer of the rank-space gate's MLP, fp32: out(t, i, bias[i] + sum_j
@@ -445,6 +447,92 @@ __device__ __forceinline__ void tanh_gate_tokens(int cnt, int r, int h, const fl
     });
     __syncthreads();
   }
+}
+
+// NP pairs of raw codes (natural K order, one code per 16-bit lane) to
+// dequantised act-dtype pairs: (q - z) exact, then one rounding of its
+// product with s (fp16: the biased code minus 1024 + z, an exact integer, in
+// packed half math; bf16: in fp32, then rounded).
+template <int DT, int NP>
+__device__ __forceinline__ void dequant_pairs(const uint32_t (&p)[NP], float s, int z,
+                                              uint32_t (&out)[NP]) {
+  if constexpr (DT == DT_F16) {
+    const _Float16 zb = (_Float16)(1024 + z);
+    const f16x2 nz = f16x2{-zb, -zb};
+    const f16x2 s2 = f16x2{(_Float16)s, (_Float16)s};
+#pragma unroll
+    for (int i = 0; i < NP; ++i) {
+      const f16x2 q = __builtin_bit_cast(f16x2, p[i] | 0x64006400u);
+      out[i] = __builtin_bit_cast(uint32_t, (q + nz) * s2);
+    }
+  } else {
+    const float c = -(float)z * s;  // exact, and so is the fused multiply-add
+#pragma unroll
+    for (int i = 0; i < NP; ++i)
+      out[i] = pack_bf16(__builtin_fmaf((float)(p[i] & 0xFFFFu), s, c), __builtin_fmaf((float)(p[i] >> 16), s, c));
+  }
+}
+
+// One packed word of 4-bit codes as exact fp16 integers q - z in natural order:
+// pairs (q0,q1), (q2,q3), (q4,q5), (q6,q7). Each byte, copied to both halves
+// of a register, gives 1024 + q_even and 1024 + 16 q_odd by one mask-and-or
+// (km 0x00F0000F, kg 0x64006400, in registers so that it is one
+// instruction), and one fused multiply-add with (1, 1/16) and `cz` =
+// exact_cz(z), exact, the integers: 12 instructions per word.
+__device__ __forceinline__ uint32_t exact_cz(uint32_t z) {
+  return 0xD400E400u + z * 0x00100001u;  // fp16 -(1024 + z) | -(64 + z) << 16
+}
+__device__ __forceinline__ u32x4 exact_word(uint32_t w, uint32_t km, uint32_t kg, uint32_t cz) {
+  const f16x2 m = f16x2{(_Float16)1.f, (_Float16)0.0625f}, c = __builtin_bit_cast(f16x2, cz);
+  u32x4 r;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const uint32_t t = (__builtin_amdgcn_perm(0u, w, 0x0C000C00u | (uint32_t)i * 0x00010001u) & km) | kg;
+    r[i] = __builtin_bit_cast(uint32_t, __builtin_elementwise_fma(__builtin_bit_cast(f16x2, t), m, c));
+  }
+  return r;
+}
+
+// The same word as biased values (fp16 1024 + q, bf16 128 + q) in natural
+// order, nine instructions (km 0x000F000F, kg the magic pair, in registers).
+__device__ __forceinline__ u32x4 biased_word_nat(uint32_t w, uint32_t km, uint32_t kg) {
+  const uint32_t hi = w >> 4;
+  return u32x4{(__builtin_amdgcn_perm(hi, w, 0x0C040C00u) & km) | kg, (__builtin_amdgcn_perm(hi, w, 0x0C050C01u) & km) | kg,
+               (__builtin_amdgcn_perm(hi, w, 0x0C060C02u) & km) | kg, (__builtin_amdgcn_perm(hi, w, 0x0C070C03u) & km) | kg};
+}
+
+// One packed word of 4-bit codes, dequantised in natural order: (q - z) exact,
+// then one rounding of its product with s. fp16: the exact integers times s in
+// packed half math. bf16: q s - z s in one fp32 fused multiply-add (z s and
+// the result are exact: at most 16 significant bits), then rounded.
+template <int DT>
+__device__ __forceinline__ void dequant_word_pairs(uint32_t w, float s, int z, uint32_t (&out)[4]) {
+  if constexpr (DT == DT_F16) {
+    const u32x4 q = exact_word(w, opaque_v(0x00F0000Fu), opaque_v(0x64006400u), exact_cz((uint32_t)z));
+    const f16x2 s2 = f16x2{(_Float16)s, (_Float16)s};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) out[i] = __builtin_bit_cast(uint32_t, __builtin_bit_cast(f16x2, (uint32_t)q[i]) * s2);
+  } else {
+    const uint32_t lo = w & 0x0F0F0F0Fu, hi = (w >> 4) & 0x0F0F0F0Fu;
+    const float c = -(float)z * s;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float a0 = __builtin_fmaf((float)((lo >> (8 * i)) & 0xFFu), s, c);
+      const float a1 = __builtin_fmaf((float)((hi >> (8 * i)) & 0xFFu), s, c);
+      out[i] = pack_bf16(a0, a1);
+    }
+  }
+}
+
+// Pairs P0 .. P0 + NP - 1 of a block of 3-bit codes (three words in w),
+// dequantised in natural order.
+template <int DT, int P0, int NP>
+__device__ __forceinline__ void dequant_block3_pairs(const u32x4& w, float s, int z,
+                                                     uint32_t (&out)[NP]) {
+  uint32_t p[NP];
+#pragma unroll
+  for (int i = 0; i < NP; ++i) p[i] = w3_pair(w, P0 + i, 0u);
+  dequant_pairs<DT, NP>(p, s, z, out);
 }
 
 // Raise a kernel's dynamic-LDS limit when a launch needs more than 64 KB.

@@ -15,58 +15,6 @@ namespace spear {
 // per block into the LDS tile, (q - z) exact then times s with one rounding
 // (fp16) or via fp32 (bf16). Four waves, 2x2, each 64x64 = 4x4 MFMA tiles.
 // ---------------------------------------------------------------------------
-// NP pairs of raw codes (natural K order, one code per 16-bit lane) to
-// dequantised act-dtype pairs: (q - z) exact, then one rounding of its
-// product with s (fp16: the biased code minus 1024 + z, an exact integer, in
-// packed half math; bf16: in fp32, then rounded).
-template <int DT, int NP>
-__device__ __forceinline__ void dequant_pairs(const uint32_t (&p)[NP], float s, int z,
-                                              uint32_t (&out)[NP]) {
-  if constexpr (DT == DT_F16) {
-    const _Float16 zb = (_Float16)(1024 + z);
-    const f16x2 nz = f16x2{-zb, -zb};
-    const f16x2 s2 = f16x2{(_Float16)s, (_Float16)s};
-#pragma unroll
-    for (int i = 0; i < NP; ++i) {
-      const f16x2 q = __builtin_bit_cast(f16x2, p[i] | 0x64006400u);
-      out[i] = __builtin_bit_cast(uint32_t, (q + nz) * s2);
-    }
-  } else {
-    const float zf = (float)z;
-#pragma unroll
-    for (int i = 0; i < NP; ++i) {
-      const float a0 = ((float)(p[i] & 0xFFFF) - zf) * s;
-      const float a1 = ((float)(p[i] >> 16) - zf) * s;
-      out[i] = (uint32_t)f2act<DT>(a0) | ((uint32_t)f2act<DT>(a1) << 16);
-    }
-  }
-}
-
-// One packed word of 4-bit codes, dequantised in natural order: pairs
-// (q0,q1), (q2,q3), (q4,q5), (q6,q7).
-template <int DT>
-__device__ __forceinline__ void dequant_word_pairs(uint32_t w, float s, int z, uint32_t (&out)[4]) {
-  const uint32_t lo = w & 0x0F0F0F0Fu;         // q0 q2 q4 q6
-  const uint32_t hi = (w >> 4) & 0x0F0F0F0Fu;  // q1 q3 q5 q7
-  uint32_t p[4];
-  p[0] = __builtin_amdgcn_perm(hi, lo, 0x0C040C00u);
-  p[1] = __builtin_amdgcn_perm(hi, lo, 0x0C050C01u);
-  p[2] = __builtin_amdgcn_perm(hi, lo, 0x0C060C02u);
-  p[3] = __builtin_amdgcn_perm(hi, lo, 0x0C070C03u);
-  dequant_pairs<DT, 4>(p, s, z, out);
-}
-
-// Pairs P0 .. P0 + NP - 1 of a block of 3-bit codes (three words in w),
-// dequantised in natural order.
-template <int DT, int P0, int NP>
-__device__ __forceinline__ void dequant_block3_pairs(const u32x4& w, float s, int z,
-                                                     uint32_t (&out)[NP]) {
-  uint32_t p[NP];
-#pragma unroll
-  for (int i = 0; i < NP; ++i) p[i] = w3_pair(w, P0 + i, 0u);
-  dequant_pairs<DT, NP>(p, s, z, out);
-}
-
 // ---------------------------------------------------------------------------
 // Dequantisation diagnostic, by the code the prefill GEMM dequantises its
 // weight tiles with ((q - z) exact, then one rounding of its product with s):

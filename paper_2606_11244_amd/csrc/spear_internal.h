@@ -169,6 +169,7 @@ struct GemmParams {
   // fp32 tiles [S][tiles][128 x 128] (lane-major), tile counters, and with
   // EPI_LOCAL the slices' EC accumulators [S][tiles][4096] (lane-major)
   int S;
+  int ips;                // k_gemm_r: 128-wide iterations per K-slice
   float* ypart;
   uint32_t* ctr;
   float* epart;
@@ -191,6 +192,28 @@ struct GemmParams {
   const uint16_t* b2;     // [r]
   float alpha, b_g;
   int gate, h;
+};
+// k_gemm_r: output rows per workgroup, activation stages in LDS, LDS bytes for
+// 16 MT tokens and ngb quantisation groups of the K-slice
+constexpr int kMidTN = 128;
+__host__ __device__ constexpr int mid_stages(int MT) { return MT <= 6 ? 4 : 3; }
+__host__ __device__ inline size_t mid_lds(int MT, int ngb) {
+  return (size_t)mid_stages(MT) * 16 * MT * kIterK * 2 + (size_t)kMidTN * (ngb | 1) * 4;
+}
+inline int mid_tiles(int MT, int M, int N) {
+  return ((M + 16 * MT - 1) / (16 * MT)) * ((N + kMidTN - 1) / kMidTN);
+}
+// Independent k_gemm_r calls, and independent EC pre-kernels, in one launch:
+// member i owns workgroups [start[i], start[i+1]).
+struct GemmGroup {
+  GemmParams p[kGroupMax];
+  int start[kGroupMax + 1];
+  int n;
+};
+struct EcGroup {
+  EcParams p[kGroupMax];
+  int start[kGroupMax + 1];
+  int n;
 };
 // EPI_LOCAL GEMM: the EC stage tile holds A's 16 rows and w_g (row 16)
 constexpr int kGemmEcRows = 17;
@@ -239,10 +262,10 @@ __host__ __device__ inline size_t ec_block_lds(int NW, int R1p, int h, int r) {
                              int block, size_t lds, hipStream_t st);                            \
   hipError_t launch_gemv_group_##W(int MT, int RT, int epi, const GemvGroup& g, int block,      \
                                    size_t lds, hipStream_t st);                                 \
-  hipError_t launch_gemm_##W(int epi, const GemmParams& p, hipStream_t st);
+  hipError_t launch_gemm_##W(int epi, const GemmParams& p, hipStream_t st);                      \
+  hipError_t launch_mid_##W(int MT, const GemmGroup& g, hipStream_t st);
 #define SPEAR_ACT_LAUNCHERS(D)                                                                    \
-  hipError_t launch_ec_##D(const EcParams& e, int grid, int block, int ipp, size_t lds,          \
-                           hipStream_t st);                                                      \
+  hipError_t launch_ec_##D(const EcGroup& g, int block, int ipp, size_t lds, hipStream_t st);     \
   hipError_t launch_gate_##D(const EcParams& e, int ntb, size_t lds, hipStream_t st);            \
   /* y_norm[m] = RMSNorm(y[m]) * w (one workgroup per token row) */                              \
   hipError_t launch_rmsnorm_##D(const uint16_t* y, const uint16_t* w, float eps,                 \

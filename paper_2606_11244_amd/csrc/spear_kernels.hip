@@ -220,13 +220,12 @@ __device__ __forceinline__ void ec_producer(const EcParams& e, int b, uint32_t g
     if (tid == 0) s_last = arrive_last(e.ctr + tb, (uint32_t)per_tb) ? 1 : 0;
     __syncthreads();
     if (!s_last) return;
-    // the slices' partial tiles [P][cnt][R1], summed in slice order through
-    // the wave-partials region (free now)
+    // the slices' partial tiles [P][cnt][R1], summed in slice order
     const rsrc_t rp = make_rsrc(e.upart + (size_t)tb * e.P * kTokTile * e.R1,
                                 (uint32_t)e.P * kTokTile * e.R1 * 4);
     sum_slices(rp, e.P, cnt * e.R1,
-               [&](int q, int i) { return (uint32_t)(q * kTokTile * e.R1 + i) * 4u; }, red,
-               (int)(ec_red_bytes(NW) / 4), [&](int i, float v) {
+               [&](int q, int i) { return (uint32_t)(q * kTokTile * e.R1 + i) * 4u; },
+               [&](int i, float v) {
                  const int t = i / e.R1, j = i - t * e.R1;
                  u_lds[t * e.R1p + j] = v;
                });
@@ -270,11 +269,18 @@ __device__ __forceinline__ void ec_producer(const EcParams& e, int b, uint32_t g
   }
 }
 
-// EC pre-kernel (semi-fused and chain paths): one producer per workgroup.
+// EC pre-kernel (semi-fused and chain paths): one producer per workgroup, of
+// up to kGroupMax layers in one launch (the layers of a group share no data,
+// and a launch of a few workgroups costs as much as one of a few hundred).
 template <int DT, int IPP>
-__global__ __launch_bounds__(512) void k_ec(EcParams e) {
+__global__ __launch_bounds__(512) void k_ec(EcGroup g) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  ec_producer<DT, IPP>(e, blockIdx.x, 0u, smem);
+  const int b = blockIdx.x;
+  int i = 0;
+#pragma unroll
+  for (int j = 1; j < kGroupMax; ++j)
+    if (j < g.n && b >= g.start[j]) i = j;
+  ec_producer<DT, IPP>(g.p[i], b - g.start[i], 0u, smem);
 }
 
 // Naive chain, gate launch: reads u [M][R1] and writes v [M][r].
@@ -1252,13 +1258,12 @@ __device__ __forceinline__ void gemv_body(const GemvParams& a, int bid, uint32_t
       if constexpr (EPI == EPI_FUSED) fused_exit(a);
       return;
     }
-    // every slice's [M][RB] partial, summed in slice order through the
-    // wave-partials region (free now)
+    // every slice's [M][RB] partial, summed in slice order
     const rsrc_t rp = make_rsrc(a.ypart, (uint32_t)a.S * M * N * 4);
     sum_slices(rp, a.S, M * RB, [&](int q, int i) {
       const int m = i / RB, row = i - m * RB;
       return n0 + row < N ? (uint32_t)(((size_t)q * M + m) * N + n0 + row) * 4u : kOOB;
-    }, red, a.lds_y / 4, [&](int i, float v) {
+    }, [&](int i, float v) {
       const int m = i / RB, row = i - m * RB;
       yacc[m * YS + row] = v;
     });
@@ -1267,7 +1272,7 @@ __device__ __forceinline__ void gemv_body(const GemvParams& a, int bid, uint32_t
       const rsrc_t re = make_rsrc(a.eupart, (uint32_t)((size_t)a.N / RB + 1) * a.S * M * R1 * 4);
       sum_slices(re, a.S, M * R1, [&](int q, int i) {
         return (uint32_t)(((size_t)(rg * a.S + q) * M) * R1 + i) * 4u;
-      }, red, a.lds_y / 4, [&](int i, float v) {
+      }, [&](int i, float v) {
         const int m = i / R1, j = i - m * R1;
         u_loc[m * R1p + j] = v;
       });
@@ -1396,17 +1401,18 @@ __global__ __launch_bounds__(kGemvMaxThreads, gemv_min_waves(MT, RT, EPI)) void 
 // ---------------------------------------------------------------------------
 #if SPEAR_WB == 4
 
-hipError_t SPEAR_D(launch_ec)(const EcParams& e, int grid, int block, int ipp, size_t lds,
-                     hipStream_t st) {
+hipError_t SPEAR_D(launch_ec)(const EcGroup& g, int block, int ipp, size_t lds, hipStream_t st) {
+  if (g.n < 1 || g.n > kGroupMax || g.start[0] != 0) return hipErrorInvalidValue;
+  const int grid = g.start[g.n];
   if (grid == 0) return hipSuccess;
   if (ipp == 1) {
     hipError_t err = allow_lds(k_ec<DTC, 1>, lds);
     if (err != hipSuccess) return err;
-    hipLaunchKernelGGL((k_ec<DTC, 1>), dim3(grid), dim3(block), lds, st, e);
+    hipLaunchKernelGGL((k_ec<DTC, 1>), dim3(grid), dim3(block), lds, st, g);
   } else {
     hipError_t err = allow_lds(k_ec<DTC, 2>, lds);
     if (err != hipSuccess) return err;
-    hipLaunchKernelGGL((k_ec<DTC, 2>), dim3(grid), dim3(block), lds, st, e);
+    hipLaunchKernelGGL((k_ec<DTC, 2>), dim3(grid), dim3(block), lds, st, g);
   }
   return hipGetLastError();
 }

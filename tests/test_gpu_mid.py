@@ -1,0 +1,102 @@
+"""GPU parity of the GEMM that keeps the codes in registers (17 to 128 tokens):
+its token-tile widths, K-slices and remainders, ragged rows, both code widths,
+the EC epilogue, and grouped calls that share its launch and the EC
+pre-kernel's, bit for bit the members' own calls."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import spear_oracle as O
+from paper_2606_11244_amd import synth as S
+
+from gpu_util import assert_parity, gpu_y, log, scaled_ec, zero_weight
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    yield
+
+
+@pytest.fixture
+def forced():
+    """The kernel for every GEMM call above 16 tokens, in `slices` K-slices."""
+    from paper_2606_11244_amd import spear as sp
+
+    def set_(slices=0):
+        sp.set_gemm_roles(4)
+        sp.set_gemm_slices(slices)
+    yield set_
+    sp.set_gemm_roles(0)
+    sp.set_gemm_slices(0)
+
+
+# (M, N, K, G, slices): every token-tile width and its edges, two and three
+# token tiles, iteration counts around the stages in flight (1, 5, 6, 7, 13
+# iterations per slice), rows past a tile, one group and many per slice
+SHAPES = [(17, 128, 128, 128, 1), (32, 130, 640, 0, 1), (33, 100, 768, 128, 1), (48, 256, 896, 128, 1),
+          (49, 40, 1664, 128, 2), (64, 384, 2048, 256, 4), (65, 129, 1536, 128, 2), (96, 300, 3328, 0, 2),
+          (97, 16, 1024, 128, 8), (128, 128, 2048, 1024, 4), (129, 200, 1152, 128, 1), (200, 64, 2304, 0, 2),
+          (300, 1040, 1024, 128, 2), (40, 2, 6656, 128, 4)]
+
+
+@pytest.mark.parametrize("M,N,K,G,slices", SHAPES)
+@pytest.mark.parametrize("dt,bits", [(S.F16, 4), (S.BF16, 4), (S.F16, 3), (S.BF16, 3)])
+def test_product(forced, M, N, K, G, slices, dt, bits):
+    L = S.make_layer(M=M, N=N, K=K, group_size=G, rank=0, act_dtype=dt, seed=M + N, weight_bits=bits)
+    forced(slices)
+    log(f"mid M={M} N={N} K={K} G={G} S={slices} dt={dt} bits={bits}")
+    assert_parity(gpu_y(L, path=4, with_ec=False), O.w4_linear_layer(L), "product")
+
+
+@pytest.mark.parametrize("M,N,K,rank,slices,int8", [
+    (20, 200, 1024, 16, 1, False), (33, 130, 1024, 7, 2, True), (64, 256, 2048, 64, 4, True),
+    (96, 100, 1024, 33, 1, False), (128, 128, 1024, 256, 1, False), (70, 90, 1024, 200, 8, True),
+    (130, 140, 2048, 24, 2, False)])
+@pytest.mark.parametrize("dt", [S.F16, S.BF16])
+def test_ec_epilogue(forced, M, N, K, rank, slices, int8, dt):
+    """The EC term alone, so that the bar applies to it, and the whole layer."""
+    L = S.make_layer(M=M, N=N, K=K, group_size=128, rank=rank, act_dtype=dt, seed=M + rank, ab_int8=int8)
+    forced(slices)
+    log(f"mid EC M={M} N={N} r={rank} S={slices} int8={int8} dt={dt}")
+    assert_parity(gpu_y(L, path=4), O.w4ec_linear(L), "layer")
+    Z = zero_weight(L) if int8 else scaled_ec(zero_weight(L), 30)
+    assert_parity(gpu_y(Z, path=4), O.w4ec_linear(Z), "EC term")
+
+
+@pytest.mark.parametrize("M,K,ranks", [
+    (24, 1024, (0, 0, 0)), (20, 1024, (32, 32, 32)), (24, 8192, (16, 0, 16)), (40, 2048, (64, 0, 64)),
+    (64, 1024, (24, 33, 0)), (90, 2048, (0, 32, 0)), (300, 1024, (32, 64, 32)), (8, 4096, (32, 32, 0)),
+    (20, 1024, (0, 32, 0))])
+def test_group_is_the_members_own_calls(M, K, ranks):
+    """Products that share a launch, EC pre-kernels that share one (also where
+    the products do not: beyond 128 tokens, and the decode GEMV), alone and
+    beside members that share nothing, on one workspace twice in a row."""
+    from paper_2606_11244_amd import spear as sp
+    dls, members, alone = [], [], []
+    for i, (N, r) in enumerate(zip((520, 128, 1100), ranks)):
+        dl = sp.DeviceLayer(S.make_layer(M=M, N=N, K=K, group_size=128, rank=r, seed=M + i, ec_std=0.05))
+        prob = dl.problem()
+        ws = sp.allocate_workspace(prob, r > 0)
+        y = torch.empty_like(dl.y)
+        (dl.run_ec if r > 0 else dl.run_w4)(prob, ws, y=y)
+        dls.append(dl)
+        alone.append(y)
+        members.append(dl.member(prob, with_ec=r > 0))
+    log(f"group M={M} K={K} ranks={ranks} launches={sp.group_launches(members)}")
+    ws = torch.zeros(max(256, sp.group_workspace(members)), dtype=torch.uint8, device="cuda")
+    for _ in range(2):
+        for dl in dls:
+            dl.y.fill_(7.0)
+        sp.w4ec_linear_group(members, ws)
+        torch.cuda.synchronize()
+        for dl, y in zip(dls, alone):
+            assert torch.equal(dl.y.view(torch.int16), y.view(torch.int16))
+    for dl, r in zip(dls, ranks):
+        got = dl.y.float().cpu().numpy().astype(np.float64)
+        assert_parity(got, O.w4ec_linear(dl.layer) if r else O.w4_linear_layer(dl.layer), "group")
