@@ -182,6 +182,49 @@ MidShape mid_shape(int64_t M, int64_t N, int IT, int G, int ngroups) {
   return m;
 }
 
+// LDS of a GEMV block: [x slice | wave partials | gather scratch]
+// [yacc] [EC u/hidden/v] [rows of B] [scales and zero points]; the x
+// slice is staged only while the whole layout fits the CU's LDS.
+void gemv_layout(int64_t M, Resolved& z, bool local, bool fused) {
+  const int RB = 16 * z.RT;
+  z.xstride = z.ips * kIterK * 2 + 16;
+  const size_t xbytes = (size_t)M * z.xstride;
+  auto layout = [&](bool xl) {
+    const int rtw = z.RT + (local ? kLocalTiles : 0);  // wave partial tiles
+    size_t U = std::max((size_t)z.NW * rtw * z.MT * 1024, (size_t)z.S * 4);
+    if (xl) U = std::max(U, xbytes);
+    z.lds_y = (int)align_up(U, 16);
+    z.lds_e = z.lds_y + z.RT * z.MT * 1024;
+    z.lds_b = z.lds_g = z.lds_ev = z.lds_e;
+    if (local) {
+      // u [16 MT][R1p] and v [16 MT][r] (and the tanh-MLP gate's hidden
+      // layer), the rows of B, the staged A, w_g
+      const size_t hid = z.gate == GATE_TANH ? (size_t)local_tanh_cap((int)M, z.h) * z.h * 4 : 0;
+      z.lds_b = (int)align_up(z.lds_e + (size_t)16 * z.MT * (z.R1p + z.r) * 4 + hid, 16);
+      z.bpre = (z.r % 8) == 0 && RB * z.r / 8 <= 2 * 64 * z.NW;
+      z.lds_a = (int)align_up(z.lds_b + (z.bpre ? (size_t)RB * z.r * 2 : 0), 16);
+      z.lds_g = z.lds_ev = (int)(z.lds_a + (size_t)17 * (z.ips * kIterK + 8) * 2);
+    } else if (z.ec) {
+      z.lds_b = (int)(z.lds_e + ec_lds_bytes(z.R1p, z.h, z.r));
+      z.bpre = (z.r % 8) == 0 && RB * z.r / 8 <= 2 * 64 * z.NW;
+      z.lds_g = (int)align_up(z.lds_b + (z.bpre ? (size_t)RB * z.r * 2 : 0), 16);
+      z.lds_ev = z.lds_g;
+      if (fused && z.ec_mode == EC_GATHER)
+        z.lds_ev = (int)(z.lds_g + (size_t)z.P * kTokTile * z.R1 * 4);
+    }
+    z.lds_sz = z.lds_ev + (z.ec && !local ? z.RT * z.MT * 1024 : 0);
+    const int ipg = z.G / kIterK;
+    const int ngb = (int)std::min<int64_t>(z.ngroups, cdiv(z.ips, ipg) + 1);
+    z.lds_gemv = z.lds_sz + (size_t)RB * (ngb | 1) * 4;
+  };
+  z.xlds = xbytes <= kXLdsMax;
+  layout(z.xlds);
+  if (z.xlds && std::max(z.lds_gemv, z.lds_prod) > kMaxLds) {
+    z.xlds = 0;
+    layout(false);
+  }
+}
+
 spear_status_t resolve(const spear_problem_t* p, bool with_ec, Resolved* R, int rt_force = 0) {
   spear_status_t st = validate_shape(p, with_ec);
   if (st != SPEAR_OK) return st;
@@ -515,46 +558,7 @@ spear_status_t resolve(const spear_problem_t* p, bool with_ec, Resolved* R, int 
   }
 
   if (z.gemv) {
-    // LDS of a GEMV block: [x slice | wave partials | gather scratch]
-    // [yacc] [EC u/hidden/v] [rows of B] [scales and zero points]; the x
-    // slice is staged only while the whole layout fits the CU's LDS
-    const int RB = 16 * z.RT;
-    z.xstride = z.ips * kIterK * 2 + 16;
-    const size_t xbytes = (size_t)M * z.xstride;
-    auto layout = [&](bool xl) {
-      const int rtw = z.RT + (local ? kLocalTiles : 0);  // wave partial tiles
-      size_t U = std::max((size_t)z.NW * rtw * z.MT * 1024, (size_t)z.S * 4);
-      if (xl) U = std::max(U, xbytes);
-      z.lds_y = (int)align_up(U, 16);
-      z.lds_e = z.lds_y + z.RT * z.MT * 1024;
-      z.lds_b = z.lds_g = z.lds_ev = z.lds_e;
-      if (local) {
-        // u [16 MT][R1p] and v [16 MT][r] (and the tanh-MLP gate's hidden
-        // layer), the rows of B, the staged A, w_g
-        const size_t hid = z.gate == GATE_TANH ? (size_t)local_tanh_cap((int)M, z.h) * z.h * 4 : 0;
-        z.lds_b = (int)align_up(z.lds_e + (size_t)16 * z.MT * (z.R1p + z.r) * 4 + hid, 16);
-        z.bpre = (z.r % 8) == 0 && RB * z.r / 8 <= 2 * 64 * z.NW;
-        z.lds_a = (int)align_up(z.lds_b + (z.bpre ? (size_t)RB * z.r * 2 : 0), 16);
-        z.lds_g = z.lds_ev = (int)(z.lds_a + (size_t)17 * (z.ips * kIterK + 8) * 2);
-      } else if (z.ec) {
-        z.lds_b = (int)(z.lds_e + ec_lds_bytes(z.R1p, z.h, z.r));
-        z.bpre = (z.r % 8) == 0 && RB * z.r / 8 <= 2 * 64 * z.NW;
-        z.lds_g = (int)align_up(z.lds_b + (z.bpre ? (size_t)RB * z.r * 2 : 0), 16);
-        z.lds_ev = z.lds_g;
-        if (fused && z.ec_mode == EC_GATHER)
-          z.lds_ev = (int)(z.lds_g + (size_t)z.P * kTokTile * z.R1 * 4);
-      }
-      z.lds_sz = z.lds_ev + (z.ec && !local ? z.RT * z.MT * 1024 : 0);
-      const int ipg = z.G / kIterK;
-      const int ngb = (int)std::min<int64_t>(z.ngroups, cdiv(z.ips, ipg) + 1);
-      z.lds_gemv = z.lds_sz + (size_t)RB * (ngb | 1) * 4;
-    };
-    z.xlds = xbytes <= kXLdsMax;
-    layout(z.xlds);
-    if (z.xlds && std::max(z.lds_gemv, z.lds_prod) > kMaxLds) {
-      z.xlds = 0;
-      layout(false);
-    }
+    gemv_layout(M, z, local, fused);
     if (std::max(z.lds_gemv, z.lds_prod) > kMaxLds) return local ? SPEAR_E_UNSUPPORTED : SPEAR_E_SHAPE;
   } else if (z.lds_prod > kMaxLds) {
     return SPEAR_E_SHAPE;
@@ -617,7 +621,10 @@ spear_status_t resolve(const spear_problem_t* p, bool with_ec, Resolved* R, int 
       const int64_t words = z.ec_mode == EC_GATHER ? (int64_t)z.P * M * z.R1 : M * z.r;
       z.direct = words <= kDirectMaxWords && z.nrg * z.S <= kDirectMaxGrid;
     }
-    if (partials) z.off_upart = take((size_t)z.ntb * z.P * kTokTile * z.R1 * 4);
+    // (the producer-fused plan reserves them too, up to 1 MiB, for a group
+    // that runs its projection in a shared pre-kernel)
+    const size_t upart = (size_t)z.ntb * z.P * kTokTile * z.R1 * 4;
+    if (partials || (fused && upart <= ((size_t)1 << 20))) z.off_upart = take(upart);
     z.off_v = take((size_t)M * z.r * 4);
     if (!z.gemv && path == SPEAR_PATH_UNFUSED_2K) {
       z.off_vh = take((size_t)M * z.vstride * 2);
@@ -1278,19 +1285,24 @@ int group_select(int32_t n, const spear_layer_call_t* calls, Resolved* z, bool* 
 }
 
 // The members outside the shared GEMV launch that share a launch with others:
-// set[i], the first member of i's shared k_gemm_r launch, or -1, and
-// ec_set[i], the same for its EC pre-kernel (semi-fused members; each runs
-// its 4-bit product on its own where set[i] is -1). Sets have at least two
-// members. They run exactly the workgroups of their own launches.
-void prefill_sets(int32_t n, const spear_layer_call_t* calls, const Resolved* z, const bool* in, int* set,
-                  int* ec_set) {
-  int key[SPEAR_GROUP_MAX], ekey[SPEAR_GROUP_MAX];
+// set[i], the first member of i's shared k_gemm_r launch, or -1; gv_set[i],
+// the same for a shared launch of the decode GEMV with an EC wave; ec_set[i],
+// the same for its EC pre-kernel (a semi-fused member outside both runs its
+// 4-bit product on its own). Sets have at least two members. They do exactly
+// the sums of their own launches in the same order: a producer-fused member
+// has its projection, in the same slices, in the shared pre-kernel, and its
+// GEMV waves in the shared launch; row tiles are brought to the set's largest
+// (z is re-planned), which no sum depends on.
+void shared_sets(int32_t n, const spear_layer_call_t* calls, Resolved* z, const bool* in, int* set,
+                 int* ec_set, int* gv_set) {
+  int key[SPEAR_GROUP_MAX], ekey[SPEAR_GROUP_MAX], gkey[SPEAR_GROUP_MAX];
   for (int i = 0; i < n; ++i) {
     const bool live = !in[i] && calls[i].prob->M > 0 && calls[i].prob->N > 0;
     const bool two = live && z[i].ec && z[i].plan.path == SPEAR_PATH_UNFUSED_2K;
     const bool w4 = live && !z[i].ec;
     key[i] = (two || w4) && !z[i].gemv && z[i].groles == 4 ? (z[i].gmid * 2 + z[i].dt) * 8 + z[i].wb : -1;
-    ekey[i] = two ? (z[i].ec_block * 4 + z[i].ec_ipp) * 2 + z[i].dt : -1;
+    const bool fused = live && z[i].ec && z[i].plan.path == SPEAR_PATH_FUSED_GEMV && z[i].off_upart;
+    gkey[i] = (two || fused) && z[i].gemv ? ((z[i].MT * 16 + z[i].NW) * 2 + z[i].dt) * 8 + z[i].wb : -1;
   }
   auto collect = [&](const int* k, int* out, int max_ctr, auto ctrs) {
     for (int i = 0; i < n; ++i) out[i] = -1;
@@ -1307,11 +1319,40 @@ void prefill_sets(int32_t n, const spear_layer_call_t* calls, const Resolved* z,
   collect(key, set, kMaxRowCounters, [&](int j) {
     return z[j].Sg > 1 ? mid_tiles(z[j].gmid, (int)calls[j].prob->M, (int)calls[j].prob->N) : 0;
   });
+  collect(gkey, gv_set, kMaxRowCounters, [&](int j) { return z[j].S > 1 ? z[j].nrg : 0; });
+  for (int i = 0; i < n; ++i) {
+    if (gv_set[i] != i) continue;
+    int rt = 0;
+    for (int j = i; j < n; ++j)
+      if (gv_set[j] == i) rt = std::max(rt, z[j].RT);
+    Resolved zz[SPEAR_GROUP_MAX];
+    bool ok = true;
+    for (int j = i; j < n; ++j) {
+      if (gv_set[j] != i) continue;
+      zz[j] = z[j];
+      zz[j].RT = rt;
+      zz[j].nrg = (int)cdiv(calls[j].prob->N, 16 * rt);
+      zz[j].ec_mode = EC_LAST;
+      zz[j].plan.path = SPEAR_PATH_UNFUSED_2K;
+      gemv_layout(calls[j].prob->M, zz[j], false, false);
+      ok = ok && std::max(zz[j].lds_gemv, zz[j].lds_prod) <= kMaxLds;
+    }
+    for (int j = n - 1; j >= i; --j) {
+      if (gv_set[j] != i) continue;
+      if (ok) z[j] = zz[j];
+      else gv_set[j] = -1;
+    }
+  }
+  for (int i = 0; i < n; ++i) {
+    const bool two = !in[i] && calls[i].prob->M > 0 && calls[i].prob->N > 0 && z[i].ec &&
+                     z[i].plan.path == SPEAR_PATH_UNFUSED_2K;
+    ekey[i] = two ? (z[i].ec_block * 4 + z[i].ec_ipp) * 2 + z[i].dt : -1;
+  }
   collect(ekey, ec_set, kMaxEcCounters, [&](int j) { return z[j].ntb; });
   // a semi-fused member's EC result must be in its own part of the workspace
   // when its 4-bit product shares a launch: it then takes the shared EC path
   for (int i = 0; i < n; ++i)
-    if (set[i] >= 0 && z[i].ec && ec_set[i] < 0) ec_set[i] = i;
+    if ((set[i] >= 0 || gv_set[i] >= 0) && z[i].ec && ec_set[i] < 0) ec_set[i] = i;
 }
 
 spear_status_t spear_group_workspace(int32_t n, const spear_layer_call_t* calls, size_t* out_bytes) {
@@ -1329,14 +1370,15 @@ spear_status_t spear_group_launches(int32_t n, const spear_layer_call_t* calls, 
   bool in[SPEAR_GROUP_MAX];
   int epi = -1, first = -1;
   const int n_in = group_select(n, calls, z, in, &epi, &first);
-  int set[SPEAR_GROUP_MAX], ec_set[SPEAR_GROUP_MAX];
-  prefill_sets(n, calls, z, in, set, ec_set);
+  int set[SPEAR_GROUP_MAX], ec_set[SPEAR_GROUP_MAX], gv_set[SPEAR_GROUP_MAX];
+  shared_sets(n, calls, z, in, set, ec_set, gv_set);
   // one launch per shared set (counted at its first member)
   int32_t launches = n_in > 0 ? 1 : 0;
   for (int i = 0; i < n; ++i) {
     if (in[i] || calls[i].prob->M == 0 || calls[i].prob->N == 0) continue;
     const int ec_launch = ec_set[i] < 0 ? 0 : ec_set[i] == i ? 1 : 0;
-    const int main_launch = set[i] < 0 ? 1 : set[i] == i ? 1 : 0;
+    const int main_set = set[i] >= 0 ? set[i] : gv_set[i];
+    const int main_launch = main_set < 0 || main_set == i ? 1 : 0;
     launches += ec_set[i] >= 0 ? ec_launch + main_launch
                 : set[i] >= 0  ? main_launch
                                : z[i].plan.num_launches;
@@ -1382,8 +1424,8 @@ spear_status_t spear_w4ec_linear_group(int32_t n, const spear_layer_call_t* call
   bool in[SPEAR_GROUP_MAX];
   int epi = -1, first = -1;
   const int n_in = group_select(n, calls, z, in, &epi, &first);
-  int set[SPEAR_GROUP_MAX], ec_set[SPEAR_GROUP_MAX];
-  prefill_sets(n, calls, z, in, set, ec_set);
+  int set[SPEAR_GROUP_MAX], ec_set[SPEAR_GROUP_MAX], gv_set[SPEAR_GROUP_MAX];
+  shared_sets(n, calls, z, in, set, ec_set, gv_set);
   // members that share nothing: each as its own call would run, in the
   // workspace a single call would use
   for (int i = 0; i < n; ++i) {
@@ -1417,7 +1459,30 @@ spear_status_t spear_w4ec_linear_group(int32_t n, const spear_layer_call_t* call
   }
   for (int k = 0; k < n; ++k) {
     const spear_layer_call_t& c = calls[k];
-    if (set[k] < 0 && ec_set[k] >= 0) {
+    if (gv_set[k] == k) {
+      GemvGroup g;
+      std::memset(&g, 0, sizeof(g));
+      size_t lds = 0;
+      int ctr = 0;
+      for (int i = k; i < n; ++i) {
+        if (gv_set[i] != k) continue;
+        const spear_layer_call_t& m = calls[i];
+        GemvParams& q = g.p[g.n];
+        q = make_gemv(m.prob, z[i], m.x, m.w, m.y, m.ec, ws + off[i]);
+        q.ec = ecp[i];
+        if (z[i].S > 1) {
+          q.rb_ctr = (uint32_t*)(ws + kCtrRows) + ctr;
+          ctr += z[i].nrg;
+        }
+        g.start[g.n + 1] = g.start[g.n] + z[i].nrg * z[i].S;
+        lds = std::max(lds, z[i].lds_gemv);
+        ++g.n;
+      }
+      st = hip_status(SPEAR_BY_WB(launch_gemv_group, z[k].wb, z[k].dt)(z[k].MT, z[k].RT, EPI_READY, g,
+                                                                       64 * (z[k].NW + 1), lds, s));
+      if (st != SPEAR_OK) return st;
+    }
+    if (set[k] < 0 && gv_set[k] < 0 && ec_set[k] >= 0) {
       st = run_2k_main(c.prob, z[k], c.x, c.w, c.ec, ecp[k], c.y, nullptr, ws + off[k], s, ws);
       if (st != SPEAR_OK) return st;
     }

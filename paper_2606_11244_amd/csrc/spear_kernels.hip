@@ -1385,8 +1385,7 @@ __global__ __launch_bounds__(kGemvMaxThreads, gemv_min_waves(MT, RT, EPI)) void 
 // writes. The member index is uniform over the workgroup.
 template <int DT, int MT, int RT, int EPI, int WB>
 __global__ __launch_bounds__(kGemvMaxThreads, gemv_min_waves(MT, RT, EPI)) void k_gemv_group(GemvGroup g) {
-  static_assert(EPI == EPI_NONE || EPI == EPI_LOCAL || EPI == EPI_LOCAL_I8,
-                "grouped launches take the variants without cross-launch state");
+  static_assert(EPI != EPI_FUSED, "grouped launches take the variants without cross-launch state");
   extern __shared__ __attribute__((aligned(16))) char smem[];
   const int b = blockIdx.x;
   int i = 0;
@@ -1524,25 +1523,27 @@ static hipError_t gemv_group_launch(int epi, const GemvGroup& g, int block, size
                                     hipStream_t st) {
   constexpr int WB = SPEAR_WB;
   const int grid = g.start[g.n];
-  hipError_t err = epi == EPI_NONE    ? allow_lds(k_gemv_group<DT, MT, RT, EPI_NONE, WB>, lds)
-                   : epi == EPI_LOCAL ? allow_lds(k_gemv_group<DT, MT, RT, EPI_LOCAL, WB>, lds)
-                                      : allow_lds(k_gemv_group<DT, MT, RT, EPI_LOCAL_I8, WB>, lds);
-  if (err != hipSuccess) return err;
-  if (epi == EPI_NONE)
-    hipLaunchKernelGGL((k_gemv_group<DT, MT, RT, EPI_NONE, WB>), dim3(grid), dim3(block), lds, st, g);
-  else if (epi == EPI_LOCAL)
-    hipLaunchKernelGGL((k_gemv_group<DT, MT, RT, EPI_LOCAL, WB>), dim3(grid), dim3(block), lds, st, g);
-  else
-    hipLaunchKernelGGL((k_gemv_group<DT, MT, RT, EPI_LOCAL_I8, WB>), dim3(grid), dim3(block), lds, st,
-                       g);
+#define SPEAR_GEMV_GROUP_GO(E)                                                                   \
+  case E: {                                                                                      \
+    hipError_t err = allow_lds(k_gemv_group<DT, MT, RT, E, WB>, lds);                            \
+    if (err != hipSuccess) return err;                                                           \
+    hipLaunchKernelGGL((k_gemv_group<DT, MT, RT, E, WB>), dim3(grid), dim3(block), lds, st, g);  \
+    break;                                                                                       \
+  }
+  switch (epi) {
+    SPEAR_GEMV_GROUP_GO(EPI_NONE)
+    SPEAR_GEMV_GROUP_GO(EPI_READY)
+    SPEAR_GEMV_GROUP_GO(EPI_LOCAL)
+    SPEAR_GEMV_GROUP_GO(EPI_LOCAL_I8)
+    default: return hipErrorInvalidValue;
+  }
+#undef SPEAR_GEMV_GROUP_GO
   return hipGetLastError();
 }
 
 hipError_t SPEAR_W(launch_gemv_group)(int MT, int RT, int epi, const GemvGroup& g,
                                       int block, size_t lds, hipStream_t st) {
-  if (g.n < 1 || g.n > kGroupMax || g.start[0] != 0 ||
-      (epi != EPI_NONE && epi != EPI_LOCAL && epi != EPI_LOCAL_I8))
-    return hipErrorInvalidValue;
+  if (g.n < 1 || g.n > kGroupMax || g.start[0] != 0) return hipErrorInvalidValue;
   const bool loc = epi == EPI_LOCAL || epi == EPI_LOCAL_I8;
   for (int i = 0; i < g.n; ++i) {
     const GemvParams& p = g.p[i];

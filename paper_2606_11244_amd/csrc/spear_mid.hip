@@ -212,7 +212,7 @@ __device__ __forceinline__ void gemm_r_body(const GemmParams& a, int bid, char* 
 #pragma unroll
   for (int jj = 0; jj < 4; ++jj) xrd[jj] = lr * kIterK + 8 * ((4 * lg + jj) ^ lr);
   const uint32_t* szl = szs + (wave * 32 + lr) * ngs;
-  const uint32_t km = opaque_v(kEx && WB == 4 ? 0x00F0000Fu : 0x000F000Fu);
+  const uint32_t km = opaque_v(DT == DT_F16 ? 0x00F0000Fu : 0x000F000Fu);
   const uint32_t kg = opaque_v(DT == DT_F16 ? 0x64006400u : 0x43004300u);
   // unpacked codes of one iteration, with the scale and bias of its fold
   struct Unpacked {
@@ -241,6 +241,12 @@ __device__ __forceinline__ void gemm_r_body(const GemmParams& a, int bid, char* 
           o.c[t][jj][e] = __builtin_bit_cast(uint32_t, __builtin_bit_cast(f16x2, (uint32_t)bq[e]) + f16x2{-zb, -zb});
       } else if constexpr (kBi) {
         o.c[t][jj] = WB == 4 ? biased_word_nat(wq[t][jj], km, kg) : unpack3_biased(wq[t], jj, kg);
+      } else if constexpr (WB == 4 && DT == DT_F16) {
+        const _Float16 s1 = __builtin_bit_cast(_Float16, (uint16_t)(sz[t] & 0xFFFFu));
+        const u32x4 q = exact_word(wq[t][jj], km, kg, exact_cz(z));
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          o.c[t][jj][e] = __builtin_bit_cast(uint32_t, __builtin_bit_cast(f16x2, (uint32_t)q[e]) * f16x2{s1, s1});
       } else if constexpr (WB == 4) {
         uint32_t r[4];
         dequant_word_pairs<DT>(wq[t][jj], o.sf[t], (int)z, r);

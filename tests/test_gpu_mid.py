@@ -72,11 +72,12 @@ def test_ec_epilogue(forced, M, N, K, rank, slices, int8, dt):
 @pytest.mark.parametrize("M,K,ranks", [
     (24, 1024, (0, 0, 0)), (20, 1024, (32, 32, 32)), (24, 8192, (16, 0, 16)), (40, 2048, (64, 0, 64)),
     (64, 1024, (24, 33, 0)), (90, 2048, (0, 32, 0)), (300, 1024, (32, 64, 32)), (8, 4096, (32, 32, 0)),
-    (20, 1024, (0, 32, 0))])
+    (20, 1024, (0, 32, 0)),
+    (1, 8192, (64, 64, 64)), (4, 8192, (64, 0, 64)), (16, 8192, (64, 20, 64)), (32, 8192, (32, 64, 32))])
 def test_group_is_the_members_own_calls(M, K, ranks):
     """Products that share a launch, EC pre-kernels that share one (also where
-    the products do not: beyond 128 tokens, and the decode GEMV), alone and
-    beside members that share nothing, on one workspace twice in a row."""
+    the products do not: beyond 128 tokens), and producer-fused decode calls
+    whose projections move to the shared pre-kernel, alone and beside members that share nothing, on one workspace twice in a row."""
     from paper_2606_11244_amd import spear as sp
     dls, members, alone = [], [], []
     for i, (N, r) in enumerate(zip((520, 128, 1100), ranks)):
