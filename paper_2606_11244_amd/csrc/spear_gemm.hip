@@ -482,22 +482,16 @@ __global__ __launch_bounds__(128 * TMW, TMW == 2 ? 2 : 1) void k_gemm(GemmParams
     }
   }
 
+  const rsrc_t ry = make_rsrc(a.y, (uint32_t)M * N * 2), rres = make_rsrc(a.res, (uint32_t)M * N * 2);
 #pragma unroll
   for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int n = n0 + wn * 64 + 16 * j + lr;
-      if (n >= N) continue;
-#pragma unroll
-      for (int e2 = 0; e2 < 4; ++e2) {
-        const int m = m0 + wm * 64 + 16 * i + 4 * lg + e2;
-        if (m < M) {
-          float v = acc[i][j][e2];
-          if (a.res) v += act2f<DT>(a.res[(size_t)m * N + n]);
-          a.y[(size_t)m * N + n] = f2act<DT>(v);
-        }
-      }
-    }
+    store_results<DT, 16>(
+        ry, rres, a.res != nullptr,
+        [&](int q) {  // q = 4 j + e2
+          const int n = n0 + wn * 64 + 16 * (q >> 2) + lr, m = m0 + wm * 64 + 16 * i + 4 * lg + (q & 3);
+          return n < N && m < M ? ((uint32_t)m * N + n) * 2 : kOOB;
+        },
+        [&](int q) { return acc[i][q >> 2][q & 3]; });
 }
 
 // ---------------------------------------------------------------------------
@@ -779,22 +773,19 @@ __global__ __launch_bounds__(256 * (1 + TNB), 1) void k_gemm_ws(GemmParams a) {
     }
   }
 
+  const rsrc_t ry = make_rsrc(a.y, (uint32_t)M * N * 2), rres = make_rsrc(a.res, (uint32_t)M * N * 2);
 #pragma unroll
   for (int i = 0; i < FM32; ++i)
 #pragma unroll
-    for (int j = 0; j < FN32; ++j) {
-      const int n = n0 + wn * 64 + 32 * j + l32;
-      if (n >= N) continue;
-#pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const int m = m0 + wm * 128 + 32 * i + 8 * (e >> 2) + 4 * lh + (e & 3);
-        if (m < M) {
-          float v = acc[i][j][e];
-          if (a.res) v += act2f<DT>(a.res[(size_t)m * N + n]);
-          a.y[(size_t)m * N + n] = f2act<DT>(v);
-        }
-      }
-    }
+    for (int j = 0; j < FN32; ++j)
+      store_results<DT, 16>(
+          ry, rres, a.res != nullptr,
+          [&](int e) {
+            const int n = n0 + wn * 64 + 32 * j + l32;
+            const int m = m0 + wm * 128 + 32 * i + 8 * (e >> 2) + 4 * lh + (e & 3);
+            return n < N && m < M ? ((uint32_t)m * N + n) * 2 : kOOB;
+          },
+          [&](int e) { return acc[i][j][e]; });
 }
 
 // ---------------------------------------------------------------------------

@@ -444,22 +444,16 @@ __device__ __forceinline__ void gemm_r_body(const GemmParams& a, int bid, char* 
     }
   }
 
+  const rsrc_t ry = make_rsrc(a.y, (uint32_t)M * N * 2), rres = make_rsrc(a.res, (uint32_t)M * N * 2);
 #pragma unroll
-  for (int t = 0; t < RT; ++t) {
-    const int n = n0 + wave * 32 + 16 * t + lr;
-    if (n >= N) continue;
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int m = m0 + 16 * mt + 4 * lg + i;
-        if (m < M) {
-          float v = acc[t * MT + mt][i];
-          if (a.res) v += act2f<DT>(a.res[(size_t)m * N + n]);
-          a.y[(size_t)m * N + n] = f2act<DT>(v);
-        }
-      }
-  }
+  for (int mt = 0; mt < MT; ++mt)
+    store_results<DT, 4 * RT>(
+        ry, rres, a.res != nullptr,
+        [&](int q) {  // q = 4 t + i
+          const int n = n0 + wave * 32 + 16 * (q >> 2) + lr, m = m0 + 16 * mt + 4 * lg + (q & 3);
+          return n < N && m < M ? ((uint32_t)m * N + n) * 2 : kOOB;
+        },
+        [&](int q) { return acc[(q >> 2) * MT + mt][q & 3]; });
 }
 
 // Up to kGroupMax independent layer calls in one launch (one for a single
