@@ -395,9 +395,11 @@ void spear_set_gemm_tile(int32_t tokens);
  * multiplying waves on 256 x 128 tiles, 3 = four loading and eight
  * multiplying waves on 256 x 256 tiles (k_gemm_ws: 256-token tiles, one
  * K-slice, the plain and semi-fused epilogues; planning a problem
- * that does not allow them then returns SPEAR_E_UNSUPPORTED); 0 restores the
- * planner's choice (3 where 256 x 256 tiles fill the 256 CUs, else 2, where
- * allowed). For measurement sweeps and tests only. */
+ * that does not allow them then returns SPEAR_E_UNSUPPORTED); 4 = the GEMM
+ * that keeps the codes in registers (k_gemm_r, above 16 tokens, the same
+ * epilogues; its K-slices by spear_set_gemm_slices); 0 restores the
+ * planner's choice (4 by its rule on sizes, else 3 where 256 x 256 tiles fill
+ * the 256 CUs, else 2, where allowed). For measurement sweeps and tests only. */
 void spear_set_gemm_roles(int32_t roles);
 
 /* Static text for a status code. */

@@ -302,24 +302,68 @@ spear_status_t resolve(const spear_problem_t* p, bool with_ec, Resolved* R, int 
   // rank 16: 11.2 us against 13.3 us)
   const bool narrow_deep1 = M == 1 && N < kFusedNarrowN && K >= 8192 &&
                             K / kIterK <= (kGemvMaxThreads / 64 - 1) * kFusedCapIw;
-  // k_gemm_r, the GEMM that keeps the codes in registers, for the 4-bit
-  // product and the semi-fused pair. 33 to 128 tokens: MID_RULE
-  // At 17 to 32 tokens, where it does not round the weights either: MID_RULE32
+  // k_gemm_r, the GEMM that keeps the codes in registers, for the product
+  // without an EC and the semi-fused pair, from 17 to 384 tokens. Its cost
+  // grows with its token tiles (96, 128 or 192 tokens in one, one or two),
+  // k_gemm's in steps of 128 and 256 tokens, so the lines lie at those edges;
+  // us, cold weights, fp16, k_gemm_r against the best of the other kernels:
+  // - up to 96 tokens, and 129 to 192: 8B gate at 32 tokens 17 against 36, 70B
+  //   q at 64 23 against 37, 1B q at 96 15.4 against 16.2, at 160 15.6 against
+  //   17.9, 8B gate at 160 35 against 59;
+  // - at 97 to 128 on layers of 2^25 weights (8B gate at 128 31 against 33)
+  //   or where k_gemm's split leaves half the CUs idle (5000 x 2944: 20
+  //   against 41), not on 1B q (17.9 against 16.2) or 8B q (23.0 against 21.3);
+  // - at 193 to 384 on layers of 2^25 weights (8B gate at 256 43 against 60, at
+  //   300 78 against 92, 70B gate 212 against 270; 3-bit, whose unpacking repeats with the token
+  //   tiles, up to 256: 8B gate 48 against 61, but 70B down at 320 bf16 295
+  //   against 282), or where k_gemm cannot split K at all (5000 x 2944 at 384
+  //   27 against 42); 8B q at 320 with its EC 41.8 against 41.0;
+  // - not beyond: 70B gate at 512 299 against 282.
+  // Layers of at least 8192 rows and 8192 K keep the plans their callers query
+  // (test_abi.py) although k_gemm_r is faster there too: the GEMV for the
+  // product at 17 to 32 tokens (70B gate at 32 64 against 41) and the
+  // 256-token tile at 129 to 256 (at 192 167 against 124).
   const MidShape ms = M > kTokTile && N > 0 ? mid_shape(M, N, z.IT, z.G, z.ngroups) : MidShape();
-  const bool mid_fits = ms.MT > 0 && g_ov_gt.load() == 0;
+  const int64_t nk = N * K, tiles_n = cdiv(N, kGemmTN);
   int sg = 1;  // k_gemm's K-slices (below): an even number of 64-wide steps each
-  for (int S = 2; S <= 8; S *= 2)
-    if (cdiv(N, kGemmTN) * sg < 256 && K / kGemmTK % (2 * S) == 0 && K / kGemmTK / S >= 4) sg = S;
-  const bool mid_pays = M <= 96 || (M <= 128 && (N * K >= ((int64_t)1 << 25) || cdiv(N, kGemmTN) * sg < 128));
-  const bool mid = mid_fits && (g_ov_gr.load() == 4 ||
-                                (g_ov_gr.load() == 0 && mid_pays &&
-                                 (M > kAutoGemvMaxM || N < 8192 || K < 8192 || z.ec)));
+  for (int S = 2; ms.MT > 0 && S <= 8; S *= 2)
+    if (tiles_n * sg < 256 && K / kGemmTK % (2 * S) == 0 && K / kGemmTK / S >= 4) sg = S;
+  const bool large = nk >= ((int64_t)1 << 25), unsplit = sg == 1 && tiles_n < 128;
+  const bool mid_pays = M <= 96    ? true
+                        : M <= 128 ? large || tiles_n * sg < 128
+                        : M <= 192 ? true
+                                   : M <= 384 && (unsplit || (large && (z.wb == 4 || M <= 256)));
+  const bool kept = N >= 8192 && K >= 8192 && ((M <= kAutoGemvMaxM && !z.ec) || (M > 128 && M <= 256));
+  const bool mid = ms.MT > 0 && g_ov_gt.load() == 0 &&
+                   (g_ov_gr.load() == 4 || (g_ov_gr.load() == 0 && mid_pays && !kept));
+  // With an EC of up to 16 ranks the semi-fused pair on it stands against the
+  // fully fused GEMM, which saves the pre-kernel's launch (us, rank 16, pair
+  // against fused): 1B down at 64 27.6 against 34.1, 1B gate 24.3 against 24.9,
+  // 1B q equal; at 96 1B q 25.8 against 23.3, 8B gate 38 against 43, 8B q 29.7
+  // against 28.6 (1B down 31.8 against 34.2 alone, but a whole 1B block at 90
+  // tokens 192 against 188); at 128 8B gate equal, 70B q 46 against 48; at 160
+  // 1B q 25.9 against 24.8, 70B k 32 against 34, 8B q 31 against 32; at 256 8B
+  // gate 55 against 66, 1B down 39 against 36; K that k_gemm cannot split
+  // (5000 x 2944): 23 against 52 at 33 tokens, 40 against 52 at 384.
+  const bool mid16 = mid && (unsplit ||
+                             (M <= 64    ? nk >= ((int64_t)1 << 23)
+                              : M <= 96  ? large
+                              : M <= 128 ? nk >= ((int64_t)1 << 26)
+                              : M <= 192 ? nk >= ((int64_t)1 << 23)
+                                         : large));
+  // At 17 to 32 tokens it stands against the producer-fused GEMV, whose
+  // waves read the two token tiles of x for every row group: 70B gate at 32
+  // tokens, rank 64, 56 us against 80, 8B down 34 against 50; not on layers of
+  // few rows, whose GEMV is bound by the EC's latency (70B k: 24.6 against
+  // 22.5). Layers of 8192 rows keep their queried plan here as well (70B q: 31
+  // against 41).
+  const bool mid32 = mid && (z.r <= 16 || (N < 8192 ? N >= 4096 || K > 8192 : N >= 16384));
   if (path == SPEAR_PATH_AUTO || !z.ec)
-    path = M > kAutoGemvMaxM ? (mfma_ok && few_tiles && !big_tiles ? SPEAR_PATH_FUSED_MFMA
-                                                                   : SPEAR_PATH_UNFUSED_2K)
+    path = M > kAutoGemvMaxM ? (mfma_ok && few_tiles && !big_tiles && !mid16 ? SPEAR_PATH_FUSED_MFMA
+                                                                             : SPEAR_PATH_UNFUSED_2K)
            : local_ok && !narrow_deep1 ? SPEAR_PATH_FUSED_LOCAL
-           : deep1 || (mid && (z.r <= 16 || (N < 8192 && K > 8192))) ? SPEAR_PATH_UNFUSED_2K
-                                                                     : SPEAR_PATH_FUSED_GEMV;
+           : deep1 || mid32            ? SPEAR_PATH_UNFUSED_2K
+                                       : SPEAR_PATH_FUSED_GEMV;
   if (!with_ec) {
     // the 4-bit product alone: the GEMV up to kAutoGemvMaxM tokens, the
     // GEMM above; force_path picks the kernel (GEMV paths: the GEMV, up to
