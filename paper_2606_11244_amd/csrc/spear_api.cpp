@@ -154,11 +154,12 @@ int gemv_rt(int MT, int kind, int64_t N, int IT, int NW, int rt_force, int waves
 // the grid has 160 workgroups (a second slice on a grid that already fills
 // most of the CUs costs more in partial tiles than it fills: 70B gate at 64
 // tokens, 224 tiles: 64 us unsplit, 72 in two slices; q, 64 tiles: 50 us
-// unsplit, 35 in two, 24 in four). MT 0: the slices' scales exceed the LDS.
+// unsplit, 35 in two, 24 in four), and at most max_s of them. MT 0: the
+// slices' scales exceed the LDS.
 struct MidShape {
   int MT = 0, S = 0, ips = 0;
 };
-MidShape mid_shape(int64_t M, int64_t N, int IT, int G, int ngroups) {
+MidShape mid_shape(int64_t M, int64_t N, int IT, int G, int ngroups, int max_s) {
   MidShape m;
   const int64_t tms = cdiv(M, 128);
   for (int mt : {2, 3, 4, 6, 8})
@@ -174,7 +175,7 @@ MidShape mid_shape(int64_t M, int64_t N, int IT, int G, int ngroups) {
     m.S = g_ov_gs.load();
     if ((m.S != 1 && m.S != 2 && m.S != 4 && m.S != 8) || !fits(m.S)) m.MT = 0;
   } else {
-    for (int S = 1; S <= 8; S *= 2)
+    for (int S = 1; S <= max_s; S *= 2)
       if ((m.S == 0 || (wgs * m.S < 160 && IT / S >= 4)) && fits(S)) m.S = S;
     if (m.S == 0 || wgs * m.S > kMaxRowCounters) m.MT = 0;
   }
@@ -225,7 +226,8 @@ void gemv_layout(int64_t M, Resolved& z, bool local, bool fused) {
   }
 }
 
-spear_status_t resolve(const spear_problem_t* p, bool with_ec, Resolved* R, int rt_force = 0) {
+// mid_slices: k_gemm_r's largest K-split, 0: not on it (see resolve).
+spear_status_t resolve_plan(const spear_problem_t* p, bool with_ec, Resolved* R, int rt_force, int mid_slices) {
   spear_status_t st = validate_shape(p, with_ec);
   if (st != SPEAR_OK) return st;
   Resolved& z = *R;
@@ -323,7 +325,7 @@ spear_status_t resolve(const spear_problem_t* p, bool with_ec, Resolved* R, int 
   // (test_abi.py) although k_gemm_r is faster there too: the GEMV for the
   // product at 17 to 32 tokens (70B gate at 32 64 against 41) and the
   // 256-token tile at 129 to 256 (at 192 167 against 124).
-  const MidShape ms = M > kTokTile && N > 0 ? mid_shape(M, N, z.IT, z.G, z.ngroups) : MidShape();
+  const MidShape ms = M > kTokTile && N > 0 ? mid_shape(M, N, z.IT, z.G, z.ngroups, mid_slices) : MidShape();
   const int64_t nk = N * K, tiles_n = cdiv(N, kGemmTN);
   int sg = 1;  // k_gemm's K-slices (below): an even number of 64-wide steps each
   for (int S = 2; ms.MT > 0 && S <= 8; S *= 2)
@@ -665,10 +667,7 @@ spear_status_t resolve(const spear_problem_t* p, bool with_ec, Resolved* R, int 
       const int64_t words = z.ec_mode == EC_GATHER ? (int64_t)z.P * M * z.R1 : M * z.r;
       z.direct = words <= kDirectMaxWords && z.nrg * z.S <= kDirectMaxGrid;
     }
-    // (the producer-fused plan reserves them too, up to 1 MiB, for a group
-    // that runs its projection in a shared pre-kernel)
-    const size_t upart = (size_t)z.ntb * z.P * kTokTile * z.R1 * 4;
-    if (partials || (fused && upart <= ((size_t)1 << 20))) z.off_upart = take(upart);
+    if (partials) z.off_upart = take((size_t)z.ntb * z.P * kTokTile * z.R1 * 4);
     z.off_v = take((size_t)M * z.r * 4);
     if (!z.gemv && path == SPEAR_PATH_UNFUSED_2K) {
       z.off_vh = take((size_t)M * z.vstride * 2);
@@ -688,8 +687,36 @@ spear_status_t resolve(const spear_problem_t* p, bool with_ec, Resolved* R, int 
     if (tiles > kMaxRowCounters || part >= ((size_t)1 << 31)) return SPEAR_E_SHAPE;
     z.off_gpart = take(part);
   }
+  // the producer-fused plan reserves its projection's partials too, up to
+  // 1 MiB, for a group that runs it in a shared pre-kernel; not where they
+  // would take the plan past the library's own scratch
+  if (fused && z.off_upart == 0) {
+    const size_t upart = (size_t)z.ntb * z.P * kTokTile * z.R1 * 4;
+    if (upart <= ((size_t)1 << 20) && (off > SPEAR_SCRATCH_BYTES || off + upart <= SPEAR_SCRATCH_BYTES))
+      z.off_upart = take(upart);
+  }
   z.plan.workspace_bytes = off;
   return SPEAR_OK;
+}
+
+// The plan of a call. k_gemm_r's partial tiles may take it past the library's
+// own scratch, where spear_w4ec_linear_noalloc would refuse it: it then takes
+// the most K-slices that fit, or else the kernels that would run without
+// k_gemm_r; if those do not fit either, it stands as it is (5000 x 2944 at 300
+// tokens, bf16: 17.0 MB in four slices, 1.3 MB unsplit).
+spear_status_t resolve(const spear_problem_t* p, bool with_ec, Resolved* R, int rt_force = 0) {
+  spear_status_t st = resolve_plan(p, with_ec, R, rt_force, 8);
+  if (st != SPEAR_OK || R->groles != 4 || g_ov_gr.load() == 4 || R->plan.workspace_bytes <= SPEAR_SCRATCH_BYTES)
+    return st;
+  for (int s = R->Sg / 2;; s /= 2) {
+    Resolved z;
+    if (resolve_plan(p, with_ec, &z, rt_force, s) == SPEAR_OK &&
+        z.plan.workspace_bytes <= SPEAR_SCRATCH_BYTES) {
+      *R = z;
+      return SPEAR_OK;
+    }
+    if (s == 0) return st;
+  }
 }
 
 // Bytes of the packed codes of an [N][K] weight of this code width.

@@ -6,6 +6,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import random
 import re
 
 import pytest
@@ -446,6 +447,35 @@ def test_gemm_wave_roles_rules():
         sp.set_gemm_roles(0)
         sp.set_gemm_slices(0)
         sp.set_gemm_tile(0)
+
+
+def test_register_gemm_plans_stay_within_the_library_scratch():
+    """A call whose scratch fits the library's own array on the other kernels
+    fits it on AUTO's plan too, so that spear_w4ec_linear_noalloc takes it:
+    k_gemm_r splits K only as far as that allows (ragged layers, whose tile
+    count lies between a half and a whole round, and layers whose scales force
+    a split), and the producer-fused plan reserves a group's partials only
+    where they fit."""
+    for M, N, K, G, dt, r in ((300, 5000, 2944, 128, sp.BF16, 24), (384, 5000, 2944, 128, sp.BF16, 16),
+                              (114, 8011, 8960, 128, sp.F16, 32), (225, 4248, 4992, 128, sp.F16, 32),
+                              (293, 5886, 13952, 128, sp.F16, 32), (99, 8274, 2688, 128, sp.BF16, 24),
+                              (321, 28725, 17280, 128, sp.BF16, 24), (116, 28672, 18304, 128, sp.BF16, 12)):
+        for path in (0, 4, 6):
+            p = sp.problem(M, N, K, G, dt, r, force_path=path)
+            assert sp.dispatch_plan(p).workspace_bytes <= sp.SCRATCH_BYTES, (M, N, K, path)
+    p = sp.problem(32, 60918, 16384, 128, sp.F16, 8, sp.GATE_ONE, force_path=sp.PATH_FUSED_GEMV)
+    assert sp.dispatch_plan(p).workspace_bytes == 16775680
+    rng = random.Random(0)
+    for _ in range(6000):
+        M, N, K = rng.randint(17, 400), rng.randint(1000, 30000), 128 * rng.randint(1, 180)
+        p = sp.problem(M, N, K, rng.choice((0, 128)), sp.F16, rng.choice((0, 8, 16, 32, 100, 256)))
+        sp.set_gemm_roles(1)  # the kernels beside k_gemm_r
+        try:
+            other = sp.dispatch_plan(p).workspace_bytes
+        finally:
+            sp.set_gemm_roles(0)
+        if other <= sp.SCRATCH_BYTES:
+            assert sp.dispatch_plan(p).workspace_bytes <= sp.SCRATCH_BYTES, (M, N, K, p.rank)
 
 
 def test_ceiling_library_exports():

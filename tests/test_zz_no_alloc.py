@@ -32,6 +32,7 @@ CASES = [
     (4, [(16, 2048, 8192, 64), (2, 1024, 4096, 64)]),    # semi-fused pair (GEMV)
     (0, [(200, 1024, 4096, 16), (64, 512, 2048, 16)]),   # fully fused GEMM, split-K
     (4, [(160, 512, 4096, 32), (96, 256, 2048, 32)]),    # semi-fused pair (GEMM), split-K
+    (0, [(300, 5000, 2944, 24), (72, 520, 1024, 24)]),   # k_gemm_r: its K-split kept within the scratch
 ]
 
 
