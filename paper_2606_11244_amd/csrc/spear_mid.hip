@@ -220,6 +220,25 @@ __device__ __forceinline__ void gemm_r_body(const GemmParams& a, int bid, char* 
     float sf[RT], cf[RT];
   };
   Unpacked ua, ub;
+  // code word jj of a row, dequantised with one rounding (natural order)
+  auto dequant = [&](const u32x4& wq, int jj, uint32_t sz) {
+    const uint32_t z = sz >> 16;
+    uint32_t r[4];
+    if constexpr (WB == 4 && DT == DT_F16) {
+      const _Float16 s1 = __builtin_bit_cast(_Float16, (uint16_t)(sz & 0xFFFFu));
+      const u32x4 q = exact_word(wq[jj], km, kg, exact_cz(z));
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        r[e] = __builtin_bit_cast(uint32_t, __builtin_bit_cast(f16x2, (uint32_t)q[e]) * f16x2{s1, s1});
+    } else if constexpr (WB == 4) {
+      dequant_word_pairs<DT>(wq[jj], h2f((uint16_t)(sz & 0xFFFFu)), (int)z, r);
+    } else {
+      const u32x4 bq = unpack3_biased(wq, jj, 0u);
+      const uint32_t pq[4] = {bq[0], bq[1], bq[2], bq[3]};
+      dequant_pairs<DT, 4>(pq, h2f((uint16_t)(sz & 0xFFFFu)), (int)z, r);
+    }
+    return u32x4{r[0], r[1], r[2], r[3]};
+  };
   // words 4 t + jj in [w0, w1) of an iteration's codes
   auto unpack = [&](Unpacked& o, const u32x4 (&wq)[RT], const uint32_t (&sz)[RT], int w0, int w1) {
 #pragma unroll
@@ -241,22 +260,8 @@ __device__ __forceinline__ void gemm_r_body(const GemmParams& a, int bid, char* 
           o.c[t][jj][e] = __builtin_bit_cast(uint32_t, __builtin_bit_cast(f16x2, (uint32_t)bq[e]) + f16x2{-zb, -zb});
       } else if constexpr (kBi) {
         o.c[t][jj] = WB == 4 ? biased_word_nat(wq[t][jj], km, kg) : unpack3_biased(wq[t], jj, kg);
-      } else if constexpr (WB == 4 && DT == DT_F16) {
-        const _Float16 s1 = __builtin_bit_cast(_Float16, (uint16_t)(sz[t] & 0xFFFFu));
-        const u32x4 q = exact_word(wq[t][jj], km, kg, exact_cz(z));
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          o.c[t][jj][e] = __builtin_bit_cast(uint32_t, __builtin_bit_cast(f16x2, (uint32_t)q[e]) * f16x2{s1, s1});
-      } else if constexpr (WB == 4) {
-        uint32_t r[4];
-        dequant_word_pairs<DT>(wq[t][jj], o.sf[t], (int)z, r);
-        o.c[t][jj] = u32x4{r[0], r[1], r[2], r[3]};
       } else {
-        const u32x4 bq = unpack3_biased(wq[t], jj, 0u);
-        const uint32_t pq[4] = {bq[0], bq[1], bq[2], bq[3]};
-        uint32_t r[4];
-        dequant_pairs<DT, 4>(pq, o.sf[t], (int)z, r);
-        o.c[t][jj] = u32x4{r[0], r[1], r[2], r[3]};
+        o.c[t][jj] = dequant(wq[t], jj, sz[t]);
       }
     }
   };
@@ -346,6 +351,42 @@ __device__ __forceinline__ void gemm_r_body(const GemmParams& a, int bid, char* 
   for (int q = 0; q < DW - 1; ++q)
     if (j + q < nit) step(q, j + q);  // uniform over the workgroup
   wait_vm<0>();  // the last groups' loads to LDS, before the workgroup's LDS is given up
+
+  // The biased codes of kBi (128 + q, less 128 + z afterwards) turn an infinite
+  // activation into infinity less infinity, and overflow from about 2^120 on.
+  // A wave that holds a sum that is not finite forms its tile again from the
+  // dequantised weights, which keep infinities and large values as they are.
+  if constexpr (kBi) {
+    bool lost = false;
+#pragma unroll
+    for (int i = 0; i < RT * MT; ++i)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) lost |= !(__builtin_fabsf(acc[i][e]) < __builtin_inff());
+    if (__ballot(lost) != 0) {
+#pragma unroll
+      for (int i = 0; i < RT * MT; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+      for (int q = 0; q < nit; ++q) {
+        u32x4 wq[RT];
+        uint32_t sz[RT];
+        issue_w(wq, q);
+        read_sz(sz, q);
+#pragma unroll
+        for (int jj = 0; jj < 4; ++jj) {
+          u32x4 c[RT];
+#pragma unroll
+          for (int t = 0; t < RT; ++t) c[t] = dequant(wq[t], jj, sz[t]);
+#pragma unroll
+          for (int mt = 0; mt < MT; ++mt) {
+            const int m = m0 + 16 * mt + lr;
+            const u32x4 xq = bld128(rx, m < M ? ((uint32_t)m * K + at(q) * kIterK + 32 * lg + 8 * jj) * 2 : kOOB);
+#pragma unroll
+            for (int t = 0; t < RT; ++t) acc[t * MT + mt] = mfma16<DT>(xq, c[t], acc[t * MT + mt]);
+          }
+        }
+      }
+    }
+  }
 
   // v_hi and v_lo of the tile's tokens for the epilogue, [2][TM][vstride + 8]
   // in LDS (the stages are free once every wave is here); requested before

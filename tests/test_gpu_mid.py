@@ -11,7 +11,7 @@ import torch
 from oracle import spear_oracle as O
 from paper_2606_11244_amd import synth as S
 
-from gpu_util import assert_parity, gpu_y, log, scaled_ec, zero_weight
+from gpu_util import assert_parity, gpu_y, log, scaled_ec, with_fields, zero_weight
 
 pytestmark = pytest.mark.gpu
 
@@ -52,6 +52,36 @@ def test_product(forced, M, N, K, G, slices, dt, bits):
     forced(slices)
     log(f"mid M={M} N={N} K={K} G={G} S={slices} dt={dt} bits={bits}")
     assert_parity(gpu_y(L, path=4, with_ec=False), O.w4_linear_layer(L), "product")
+
+
+@pytest.mark.parametrize("M,slices", [(20, 1), (40, 2), (64, 1), (90, 1)])
+@pytest.mark.parametrize("dt,bits", [(S.F16, 4), (S.BF16, 4), (S.BF16, 3)])
+def test_infinite_nan_and_huge_activations(forced, M, slices, dt, bits):
+    """Infinities, NaN and (bf16) values whose products with the biased codes
+    would overflow: what the other GEMM (k_gemm) gives, infinities with their
+    signs, NaN where a zero weight meets an infinity, and the oracle's values
+    in the tokens that stay finite."""
+    from paper_2606_11244_amd import spear as sp
+    L = S.make_layer(M=M, N=200, K=1024, group_size=128, rank=0, act_dtype=dt, seed=M, weight_bits=bits)
+    x = S.from_bits(L.x, dt).copy()
+    x[3, 77], x[7, 11], x[9, 1000] = np.inf, -np.inf, np.nan
+    if dt == S.BF16:
+        x[5, 300], x[M - 1, 640] = 3e37, -2.5e38
+    L = with_fields(L, x=S.to_bits(x, dt))
+    sp.set_gemm_roles(1)
+    ref = gpu_y(L, path=4, with_ec=False)
+    forced(slices)
+    log(f"mid nonfinite M={M} S={slices} dt={dt} bits={bits}")
+    got = gpu_y(L, path=4, with_ec=False)
+    assert np.isinf(ref[[3, 7]]).mean() > 0.5 and np.isnan(ref[9]).all()
+    assert np.array_equal(np.isnan(got), np.isnan(ref))
+    assert np.array_equal(np.where(np.isinf(got), got, 0), np.where(np.isinf(ref), ref, 0))
+    rows = [m for m in range(M) if m not in (3, 7, 9)]
+    want = O.w4_linear_layer(L)[rows]
+    assert np.isfinite(got[rows]).all()
+    # per token: the huge ones must not hide the others
+    for m, y in zip(rows, want):
+        assert_parity(got[m:m + 1], y[None], f"token {m}")
 
 
 @pytest.mark.parametrize("M,N,K,rank,slices,int8", [
