@@ -378,8 +378,10 @@ void spear_set_gemv_stages(int32_t stages);
 /* Tuning hook for the prefill GEMM's K-slices (1, 2, 4 or 8; each slice an
  * even number of 64-wide K steps, else the planner and the calls return
  * SPEAR_E_UNSUPPORTED), process-wide; 0 restores the planner's choice (more
- * slices only while the tile grid alone leaves CUs idle). For measurement
- * sweeps and tests only. */
+ * slices only while the tile grid alone leaves CUs idle). While it is set the
+ * planner leaves k_gemm_r aside, unless spear_set_gemm_roles(4) forces that
+ * kernel: the slices are then its own, of any number of 128-wide iterations.
+ * For measurement sweeps and tests only. */
 void spear_set_gemm_slices(int32_t k_slices);
 
 /* Tuning hook for the prefill GEMM's token tile, process-wide: 128 (four

@@ -336,7 +336,8 @@ spear_status_t resolve_plan(const spear_problem_t* p, bool with_ec, Resolved* R,
                         : M <= 192 ? true
                                    : M <= 384 && (unsplit || (large && (z.wb == 4 || M <= 256)));
   const bool kept = N >= 8192 && K >= 8192 && ((M <= kAutoGemvMaxM && !z.ec) || (M > 128 && M <= 256));
-  const bool mid = ms.MT > 0 && g_ov_gt.load() == 0 &&
+  // (the hooks for the other GEMMs' tile and K-slices leave the call to those)
+  const bool mid = ms.MT > 0 && g_ov_gt.load() == 0 && (g_ov_gs.load() == 0 || g_ov_gr.load() == 4) &&
                    (g_ov_gr.load() == 4 || (g_ov_gr.load() == 0 && mid_pays && !kept));
   // With an EC of up to 16 ranks the semi-fused pair on it stands against the
   // fully fused GEMM, which saves the pre-kernel's launch (us, rank 16, pair
@@ -514,7 +515,7 @@ spear_status_t resolve_plan(const spear_problem_t* p, bool with_ec, Resolved* R,
       if (tiles * z.Sg < 256 && steps % (2 * S) == 0 && steps / S >= 4) z.Sg = S;
     if (g_ov_gs.load() > 0) {
       const int S = g_ov_gs.load();
-      if (steps % (2 * S) != 0 && !(mid && !fmfma)) return SPEAR_E_UNSUPPORTED;
+      if (steps % (2 * S) != 0 && (g_ov_gr.load() != 4 || fmfma)) return SPEAR_E_UNSUPPORTED;
       z.Sg = S;
     }
     // 256-token tiles in one K-slice (the plain and the semi-fused

@@ -478,6 +478,30 @@ def test_register_gemm_plans_stay_within_the_library_scratch():
             assert sp.dispatch_plan(p).workspace_bytes <= sp.SCRATCH_BYTES, (M, N, K, p.rank)
 
 
+def test_gemm_slices_hook_leaves_the_register_gemm_aside():
+    """spear_set_gemm_slices is k_gemm's hook: it refuses slices of an odd
+    number of 64-wide steps at every GEMM size, and leaves the decode plans
+    (up to 32 tokens, the GEMV) as they are without a GEMM; k_gemm_r takes it
+    only where it is itself forced."""
+    sp.set_gemm_slices(2)
+    try:
+        for M in (33, 96, 300):
+            for rank in (0, 32):
+                for K in (384, 1152, 2944):
+                    with pytest.raises(sp.SpearError) as e:
+                        _plan(M=M, N=5000, K=K, rank=rank, force_path=sp.PATH_UNFUSED_2K)
+                    assert e.value.status == -6, (M, rank, K)
+        for M in (17, 32):
+            p = _plan(M=M, N=2048, K=2048, with_ec=False)
+            assert (p.path, p.tile_m) == (sp.PATH_FUSED_GEMV, 32) and p.tile_n < 128
+        sp.set_gemm_roles(4)
+        p = _plan(M=33, N=5000, K=1152, rank=0, with_ec=False)
+        assert p.split_k == 2 and p.tile_n == 128
+    finally:
+        sp.set_gemm_roles(0)
+        sp.set_gemm_slices(0)
+
+
 def test_ceiling_library_exports():
     # the measured-ceiling kernels (measurement only) ship as their own
     # library; host-side argument checks reject bad sizes before any launch
