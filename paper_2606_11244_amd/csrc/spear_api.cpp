@@ -367,12 +367,12 @@ spear_status_t resolve_plan(const spear_problem_t* p, bool with_ec, Resolved* R,
            : local_ok && !narrow_deep1 ? SPEAR_PATH_FUSED_LOCAL
            : deep1 || mid32            ? SPEAR_PATH_UNFUSED_2K
                                        : SPEAR_PATH_FUSED_GEMV;
+  const bool want_gemv = p->force_path == SPEAR_PATH_FUSED_GEMV || p->force_path == SPEAR_PATH_FUSED_LOCAL;
   if (!with_ec) {
     // the 4-bit product alone: the GEMV up to kAutoGemvMaxM tokens, the
     // GEMM above; force_path picks the kernel (GEMV paths: the GEMV, up to
     // kGemvMaxM tokens; GEMM paths: the GEMM)
     const int fp = p->force_path;
-    const bool want_gemv = fp == SPEAR_PATH_FUSED_GEMV || fp == SPEAR_PATH_FUSED_LOCAL;
     const bool want_gemm = fp == SPEAR_PATH_FUSED_MFMA || fp == SPEAR_PATH_UNFUSED_2K ||
                            fp == SPEAR_PATH_UNFUSED_CHAIN || fp == SPEAR_PATH_OVERLAP_2K;
     if (want_gemv && M > kGemvMaxM) return SPEAR_E_UNSUPPORTED;
@@ -383,10 +383,12 @@ spear_status_t resolve_plan(const spear_problem_t* p, bool with_ec, Resolved* R,
   const bool fmfma = z.ec && path == SPEAR_PATH_FUSED_MFMA;
   // the GEMV for the GEMV paths, and under the 4-bit product of the
   // two-kernel and chain paths up to kAutoGemvMaxM tokens (the GEMM above)
-  z.gemv = !with_ec ? path == SPEAR_PATH_FUSED_GEMV &&
-                          !(mid && p->force_path != SPEAR_PATH_FUSED_GEMV && p->force_path != SPEAR_PATH_FUSED_LOCAL)
-           : path == SPEAR_PATH_FUSED_GEMV || path == SPEAR_PATH_FUSED_LOCAL ||
-                 (!fmfma && M <= kAutoGemvMaxM && !mid);
+  // (k_gemm_r above 16 tokens by its rule, unless a product alone, a call of
+  // rank 0 included, is to run on the GEMV)
+  const bool off_mid = !mid || (!z.ec && want_gemv);
+  z.gemv = !with_ec ? path == SPEAR_PATH_FUSED_GEMV && off_mid
+           : (z.ec && (path == SPEAR_PATH_FUSED_GEMV || path == SPEAR_PATH_FUSED_LOCAL)) ||
+                 (!fmfma && M <= kAutoGemvMaxM && off_mid);
   z.plan.path = path;
 
   if (M == 0 || N == 0) {

@@ -502,6 +502,19 @@ def test_gemm_slices_hook_leaves_the_register_gemm_aside():
         sp.set_gemm_slices(0)
 
 
+def test_rank_zero_plans_are_the_product_alone():
+    """A call of rank 0 runs what the product alone runs, on AUTO and with the
+    GEMV forced (up to 32 tokens)."""
+    for M in (1, 8, 16, 17, 24, 32, 33, 64, 96, 300, 512, 4096):
+        for N, K in ((2048, 2048), (5000, 2944), (8192, 8192), (1024, 8192), (512, 256)):
+            for path in (0, sp.PATH_FUSED_GEMV, sp.PATH_FUSED_LOCAL):
+                if path and M > 32:
+                    continue
+                a, b = (_plan(M=M, N=N, K=K, rank=0, force_path=path, with_ec=e) for e in (True, False))
+                for f in ("tile_m", "tile_n", "split_k", "grid", "num_launches", "workspace_bytes"):
+                    assert getattr(a, f) == getattr(b, f), (M, N, K, path, f)
+
+
 def test_ceiling_library_exports():
     # the measured-ceiling kernels (measurement only) ship as their own
     # library; host-side argument checks reject bad sizes before any launch
