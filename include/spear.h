@@ -191,8 +191,10 @@ typedef struct {
 } spear_ec_t;
 
 typedef struct {
-  int32_t path;          /* resolved SPEAR_PATH_* (never AUTO)                */
-  int32_t split_k;       /* K-slices of the 4-bit product (GEMV paths)        */
+  int32_t path;          /* resolved SPEAR_PATH_* (never AUTO); the product
+                            alone: FUSED_GEMV for the GEMV, UNFUSED_2K for a
+                            GEMM                                              */
+  int32_t split_k;       /* K-slices of the 4-bit product                     */
   int32_t ec_splits;     /* K-slices of the EC projection A x                 */
   int32_t tile_m;        /* tokens per workgroup tile                         */
   int32_t tile_n;        /* output rows per workgroup tile                    */

@@ -389,6 +389,8 @@ spear_status_t resolve_plan(const spear_problem_t* p, bool with_ec, Resolved* R,
   z.gemv = !with_ec ? path == SPEAR_PATH_FUSED_GEMV && off_mid
            : (z.ec && (path == SPEAR_PATH_FUSED_GEMV || path == SPEAR_PATH_FUSED_LOCAL)) ||
                  (!fmfma && M <= kAutoGemvMaxM && off_mid);
+  // the product alone reports the kernel it runs: the GEMV or a GEMM
+  if (!z.ec) path = z.gemv ? SPEAR_PATH_FUSED_GEMV : SPEAR_PATH_UNFUSED_2K;
   z.plan.path = path;
 
   if (M == 0 || N == 0) {
@@ -537,7 +539,7 @@ spear_status_t resolve_plan(const spear_problem_t* p, bool with_ec, Resolved* R,
       z.gips = ms.ips;
     }
     z.plan.split_k = z.Sg;
-    z.plan.tile_m = z.groles == 4 ? 128 : tm;  // k_gemm_r: at most (gmid token tiles of 16)
+    z.plan.tile_m = z.groles == 4 ? 16 * z.gmid : tm;
     z.plan.tile_n = z.groles == 3 ? 2 * kGemmTN : kGemmTN;
   }
 
@@ -615,9 +617,8 @@ spear_status_t resolve_plan(const spear_problem_t* p, bool with_ec, Resolved* R,
   z.plan.ec_splits = z.ec ? z.P : 0;
 
   // launches and grid
-  const int grid4 = z.gemv          ? z.nrg * z.S
-                    : z.groles == 4 ? mid_tiles(z.gmid, (int)M, (int)N) * z.Sg
-                                    : (int)(cdiv(M, z.plan.tile_m) * cdiv(N, z.plan.tile_n)) * z.Sg;
+  const int grid4 = z.gemv ? z.nrg * z.S
+                           : (int)(cdiv(M, z.plan.tile_m) * cdiv(N, z.plan.tile_n)) * z.Sg;
   if (!z.ec || local || fmfma) {
     z.plan.num_launches = 1;
     z.plan.grid = grid4;
@@ -683,9 +684,8 @@ spear_status_t resolve_plan(const spear_problem_t* p, bool with_ec, Resolved* R,
     z.off_ypart = take((size_t)z.S * M * N * 4);
   }
   if (!z.gemv && z.Sg > 1) {
-    const int tok = z.groles == 4 ? 16 * z.gmid : z.plan.tile_m;
-    const int64_t tiles = cdiv(M, tok) * cdiv(N, kGemmTN);
-    const size_t part = (size_t)z.Sg * tiles * tok * kGemmTN * 4;
+    const int64_t tiles = cdiv(M, z.plan.tile_m) * cdiv(N, kGemmTN);
+    const size_t part = (size_t)z.Sg * tiles * z.plan.tile_m * kGemmTN * 4;
     // the kernel addresses the partial tiles with 32-bit offsets
     if (tiles > kMaxRowCounters || part >= ((size_t)1 << 31)) return SPEAR_E_SHAPE;
     z.off_gpart = take(part);

@@ -96,9 +96,16 @@ def test_plan_phase_aware_dispatch():
         assert p.path == sp.PATH_FUSED_MFMA and p.num_launches == 1, M
         p = _plan(M=M, rank=32)
         assert p.path == sp.PATH_UNFUSED_2K and p.tile_n == 128, M
-    # the 4-bit product alone: GEMV up to 32 tokens, GEMM above; force_path
-    # picks either kernel
-    assert _plan(M=32, with_ec=False).path == sp.PATH_FUSED_GEMV
+    # the 4-bit product alone: GEMV up to 16 tokens, a GEMM above (up to 32 on
+    # layers of 8192 rows and 8192 K); force_path picks either kernel
+    assert _plan(M=16, with_ec=False).path == sp.PATH_FUSED_GEMV
+    for M in (17, 32):
+        p = _plan(M=M, with_ec=False)
+        assert p.path == sp.PATH_UNFUSED_2K and (p.tile_m, p.tile_n) == (32, 128), M
+        p = _plan(M=M, with_ec=False, force_path=sp.PATH_FUSED_GEMV)
+        assert p.path == sp.PATH_FUSED_GEMV and p.tile_n < 128, M
+        p = _plan(M=M, N=8192, K=8192, with_ec=False)
+        assert p.path == sp.PATH_FUSED_GEMV and p.tile_n < 128, M
     assert _plan(M=33, with_ec=False).path == sp.PATH_UNFUSED_2K
     assert _plan(M=4, with_ec=False, force_path=sp.PATH_UNFUSED_2K).tile_n == 128
     assert _plan(M=64, with_ec=False, force_path=sp.PATH_FUSED_GEMV).path == sp.PATH_FUSED_GEMV
@@ -345,7 +352,7 @@ def test_prefill_tile_rule():
     weights once a quarter of the CUs have one."""
     def tm(M, N, K, rank=64):
         return _plan(M=M, N=N, K=K, rank=rank).tile_m
-    assert tm(64, 28672, 8192) == 128 and tm(128, 28672, 8192) == 128
+    assert tm(64, 28672, 8192) == 64 and tm(128, 28672, 8192) == 128  # k_gemm_r's tiles
     assert tm(192, 28672, 8192) == 256
     assert tm(256, 8192, 8192) == 256          # 70B q: 64M weights
     assert tm(256, 2048, 8192, rank=16) == 128  # 1B down: 16M weights
@@ -511,8 +518,22 @@ def test_rank_zero_plans_are_the_product_alone():
                 if path and M > 32:
                     continue
                 a, b = (_plan(M=M, N=N, K=K, rank=0, force_path=path, with_ec=e) for e in (True, False))
-                for f in ("tile_m", "tile_n", "split_k", "grid", "num_launches", "workspace_bytes"):
-                    assert getattr(a, f) == getattr(b, f), (M, N, K, path, f)
+                assert a.as_dict() == b.as_dict(), (M, N, K, path)
+
+
+def test_register_gemm_plan_is_the_launch():
+    """k_gemm_r's plans give its token tile (the fewest 16-token tiles of at
+    most 128 tokens), from which the grid follows; k_gemm's edges just outside
+    the rule keep theirs."""
+    for M, tile in ((17, 32), (33, 48), (49, 64), (65, 96), (96, 96), (129, 96), (193, 128), (300, 128), (384, 128)):
+        for rank in (0, 24):
+            p = _plan(M=M, N=5000, K=2944, rank=rank)
+            assert p.path == sp.PATH_UNFUSED_2K and (p.tile_m, p.tile_n) == (tile, 128), (M, rank)
+            assert p.grid == -(-M // tile) * 40 * p.split_k, (M, rank)
+    assert _plan(M=16, N=5000, K=2944, rank=0).path == sp.PATH_FUSED_GEMV
+    # 385 tokens: k_gemm, which cannot split this K (23 iterations)
+    p = _plan(M=385, N=5000, K=2944, rank=0)
+    assert (p.tile_m, p.split_k, p.grid) == (128, 1, 4 * 40)
 
 
 def test_ceiling_library_exports():

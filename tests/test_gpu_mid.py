@@ -135,15 +135,23 @@ def test_group_is_the_members_own_calls(M, K, ranks):
 
 @pytest.mark.parametrize("M,N,K,rank", [
     (33, 4100, 2048, 16), (64, 4100, 2048, 8), (96, 4200, 8192, 16), (129, 300, 1024, 24), (192, 8200, 1024, 12),
-    (193, 260, 640, 24), (300, 260, 640, 16), (384, 130, 384, 0)])
+    (193, 260, 2944, 24), (300, 260, 2944, 16), (384, 130, 2944, 0)])
 @pytest.mark.parametrize("dt,bits", [(S.F16, 4), (S.BF16, 4), (S.BF16, 3)])
 def test_auto_takes_it(M, N, K, rank, dt, bits):
-    """AUTO at the edges of its sizes (the kernel's 128-row tiles, K-slices and
-    semi-fused launches as planned), whole layers against the oracle."""
+    """AUTO at the edges of its sizes: the plan is the one that forcing the
+    kernel gives, and not the one of the other kernels, and whole layers meet
+    the oracle."""
     from paper_2606_11244_amd import spear as sp
     L = S.make_layer(M=M, N=N, K=K, group_size=128, rank=rank, act_dtype=dt, seed=M + N, weight_bits=bits)
-    p = sp.dispatch_plan(sp.problem(M, N, K, 128, dt, rank, L.gate_kind, 0, sp.PATH_AUTO, bits), rank > 0)
-    assert p.path == sp.PATH_UNFUSED_2K and (p.tile_m, p.tile_n) == (128, 128)
+
+    def plan(roles):
+        sp.set_gemm_roles(roles)
+        try:
+            return sp.dispatch_plan(sp.problem(M, N, K, 128, dt, rank, L.gate_kind, 0, sp.PATH_AUTO, bits),
+                                    rank > 0).as_dict()
+        finally:
+            sp.set_gemm_roles(0)
+    assert plan(0) == plan(4) != plan(1)
     log(f"mid AUTO M={M} N={N} K={K} r={rank} dt={dt} bits={bits}")
     ref = O.w4ec_linear(L) if rank else O.w4_linear_layer(L)
     assert_parity(gpu_y(L, path=0, with_ec=rank > 0), ref, "auto")
