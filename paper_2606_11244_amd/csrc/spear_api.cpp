@@ -1375,7 +1375,9 @@ void shared_sets(int32_t n, const spear_layer_call_t* calls, Resolved* z, const 
     const bool two = live && z[i].ec && z[i].plan.path == SPEAR_PATH_UNFUSED_2K;
     const bool w4 = live && !z[i].ec;
     key[i] = (two || w4) && !z[i].gemv && z[i].groles == 4 ? (z[i].gmid * 2 + z[i].dt) * 8 + z[i].wb : -1;
-    const bool fused = live && z[i].ec && z[i].plan.path == SPEAR_PATH_FUSED_GEMV && z[i].off_upart;
+    // (a member that asks for the producer-fused path stays on it)
+    const bool fused = live && z[i].ec && z[i].plan.path == SPEAR_PATH_FUSED_GEMV && z[i].off_upart &&
+                       calls[i].prob->force_path == SPEAR_PATH_AUTO;
     gkey[i] = (two || fused) && z[i].gemv ? ((z[i].MT * 16 + z[i].NW) * 2 + z[i].dt) * 8 + z[i].wb : -1;
   }
   auto collect = [&](const int* k, int* out, int max_ctr, auto ctrs) {

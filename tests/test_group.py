@@ -193,3 +193,41 @@ def test_group_launches_beyond_the_gemv_and_empty_members():
     # a NULL out pointer
     arr, keep = _calls(_qkv(1))
     assert sp.LIB.spear_group_launches(3, arr, None) == -1
+
+
+def _sized(M, K, ranks, Ns=(520, 128, 1100), path=0):
+    return [sp.problem(M, N, K, 128, sp.F16, r, force_path=path) for N, r in zip(Ns, ranks)], [r > 0 for r in ranks]
+
+
+def test_group_launches_shared_ec_and_gemm():
+    # (M, K, ranks, launches): products on k_gemm_r share one launch (24), and
+    # with EC members one pre-kernel and one GEMM (20 to 90 tokens, ranks may
+    # differ); at 300 tokens of a small layer the members' GEMM is k_gemm, one
+    # launch each, behind a shared pre-kernel; local-EC members share theirs
+    # beside a product on k_gemm_r; decode members with an EC share a
+    # pre-kernel and a GEMV, a product beside them has its own
+    for M, K, ranks, want in ((24, 1024, (0, 0, 0), 1), (20, 1024, (32, 32, 32), 2), (20, 1024, (0, 32, 0), 2),
+                              (64, 1024, (24, 33, 0), 2), (90, 2048, (0, 32, 0), 2), (300, 1024, (32, 64, 32), 4),
+                              (24, 8192, (16, 0, 16), 2), (8, 4096, (32, 32, 0), 3), (1, 8192, (64, 64, 64), 2),
+                              (16, 8192, (64, 20, 64), 2), (4, 8192, (64, 0, 64), 3), (32, 8192, (32, 64, 32), 2)):
+        probs, ecs = _sized(M, K, ranks)
+        assert _launches(probs, ecs) == (0, want), (M, K, ranks)
+    # members of another token tile, dtype or code width do not share
+    probs, ecs = _sized(20, 1024, (0, 0))
+    probs[1] = sp.problem(40, 128, 1024, 128, sp.F16, 0)
+    assert _launches(probs, ecs) == (0, 2)
+    probs[1] = sp.problem(20, 128, 1024, 128, sp.BF16, 0)
+    assert _launches(probs, ecs) == (0, 2)
+    probs[1] = sp.problem(20, 128, 1024, 128, sp.F16, 0, weight_bits=3)
+    assert _launches(probs, ecs) == (0, 2)
+
+
+def test_group_members_keep_a_forced_path():
+    # the producer-fused path, when asked for, is not turned into the shared
+    # pre-kernel and GEMV: every member its own launch
+    for M, ranks in ((1, (64, 64, 64)), (16, (64, 20, 64))):
+        probs, ecs = _sized(M, 8192, ranks, path=sp.PATH_FUSED_GEMV)
+        assert _launches(probs, ecs) == (0, 3), M
+        # two on AUTO beside one that asks for it
+        auto, _ = _sized(M, 8192, ranks)
+        assert _launches([probs[0]] + auto[1:], ecs) == (0, 3), M
