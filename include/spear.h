@@ -366,15 +366,17 @@ int32_t spear_set_wait_polls(int32_t polls);
  * tiles per workgroup (1, 2 or 4 for up to 32 tokens; 1 or 2 above), K-slices
  * per row group, and waves per workgroup (1..8). 0 restores the planner's
  * choice for that field. A combination that is not compiled in makes the
- * planner and the calls return SPEAR_E_UNSUPPORTED. For measurement sweeps
- * only. */
+ * planner and the calls return SPEAR_E_UNSUPPORTED. While it is set the
+ * planner leaves k_gemm_r aside up to 32 tokens, unless
+ * spear_set_gemm_roles(4) forces that kernel. For measurement sweeps only. */
 void spear_set_gemv_shape(int32_t row_tiles, int32_t k_slices, int32_t waves);
 
 /* Tuning hook for the decode GEMV's pipeline depth, process-wide: stages of
  * packed codes in flight per wave, 2 or 4 (4: one token tile, the 4-bit
  * product alone, the producer-fused and the semi-fused variants; else the
  * planner and the calls return SPEAR_E_UNSUPPORTED); 0 restores the
- * planner's choice. For measurement sweeps and tests only. */
+ * planner's choice. Leaves k_gemm_r aside as spear_set_gemv_shape does. For
+ * measurement sweeps and tests only. */
 void spear_set_gemv_stages(int32_t stages);
 
 /* Tuning hook for the prefill GEMM's K-slices (1, 2, 4 or 8; each slice an

@@ -336,8 +336,12 @@ spear_status_t resolve_plan(const spear_problem_t* p, bool with_ec, Resolved* R,
                         : M <= 192 ? true
                                    : M <= 384 && (unsplit || (large && (z.wb == 4 || M <= 256)));
   const bool kept = N >= 8192 && K >= 8192 && ((M <= kAutoGemvMaxM && !z.ec) || (M > 128 && M <= 256));
-  // (the hooks for the other GEMMs' tile and K-slices leave the call to those)
-  const bool mid = ms.MT > 0 && g_ov_gt.load() == 0 && (g_ov_gs.load() == 0 || g_ov_gr.load() == 4) &&
+  // (the hooks for the other GEMMs' tile and K-slices, and up to 32 tokens the
+  // GEMV's, leave the call to those kernels)
+  const bool gemv_hook = M <= kAutoGemvMaxM && (g_ov_rt.load() > 0 || g_ov_s.load() > 0 ||
+                                                g_ov_nw.load() > 0 || g_ov_nst.load() > 0);
+  const bool mid = ms.MT > 0 && g_ov_gt.load() == 0 &&
+                   ((g_ov_gs.load() == 0 && !gemv_hook) || g_ov_gr.load() == 4) &&
                    (g_ov_gr.load() == 4 || (g_ov_gr.load() == 0 && mid_pays && !kept));
   // With an EC of up to 16 ranks the semi-fused pair on it stands against the
   // fully fused GEMM, which saves the pre-kernel's launch (us, rank 16, pair

@@ -509,6 +509,41 @@ def test_gemm_slices_hook_leaves_the_register_gemm_aside():
         sp.set_gemm_slices(0)
 
 
+def test_gemv_hooks_leave_the_register_gemm_aside():
+    """spear_set_gemv_shape and spear_set_gemv_stages are the GEMV's hooks: up
+    to 32 tokens the call stays on it with the shape they ask for, and shapes
+    that are not compiled in are refused; beyond, they change nothing."""
+    auto = {(M, rank): _plan(M=M, N=4096, K=4096, rank=rank).as_dict() for M in (33, 96, 300) for rank in (0, 32)}
+    try:
+        for M in (17, 24, 32):
+            for rank in (0, 8, 32):
+                sp.set_gemv_shape(row_tiles=4, k_slices=2, waves=4)
+                for path in (sp.PATH_AUTO, sp.PATH_UNFUSED_2K, sp.PATH_UNFUSED_CHAIN, sp.PATH_OVERLAP_2K):
+                    p = _plan(M=M, N=4096, K=4096, rank=rank, force_path=path)
+                    assert (p.tile_m, p.tile_n, p.split_k) == (32, 64, 2), (M, rank, path)
+                sp.set_gemv_shape(row_tiles=3)
+                with pytest.raises(sp.SpearError) as e:
+                    _plan(M=M, N=4096, K=4096, rank=rank)
+                assert e.value.status == -6, (M, rank)
+                sp.set_gemv_shape()
+                sp.set_gemv_stages(4)  # one token tile only
+                with pytest.raises(sp.SpearError) as e:
+                    _plan(M=M, N=4096, K=4096, rank=rank)
+                assert e.value.status == -6, (M, rank)
+                sp.set_gemv_stages()
+        sp.set_gemv_shape(row_tiles=4, k_slices=2, waves=4)
+        sp.set_gemv_stages(4)
+        for (M, rank), want in auto.items():
+            assert _plan(M=M, N=4096, K=4096, rank=rank).as_dict() == want, (M, rank)
+        sp.set_gemv_stages()
+        sp.set_gemm_roles(4)
+        assert _plan(M=32, N=4096, K=4096, rank=0, with_ec=False).tile_n == 128
+    finally:
+        sp.set_gemm_roles(0)
+        sp.set_gemv_stages()
+        sp.set_gemv_shape()
+
+
 def test_rank_zero_plans_are_the_product_alone():
     """A call of rank 0 runs what the product alone runs, on AUTO and with the
     GEMV forced (up to 32 tokens)."""
