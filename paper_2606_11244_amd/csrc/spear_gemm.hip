@@ -510,8 +510,13 @@ __global__ __launch_bounds__(128 * TMW, TMW == 2 ? 2 : 1) void k_gemm(GemmParams
 // TNB = 2: 256 x 256 tiles, eight multiplying waves (two per SIMD, 144 KB
 // of LDS), twelve waves in all, at most 168 registers each.
 // WB: code width (4, or 3: three words per 32 codes).
+// PLAIN: the epilogue of 256 x 256 tiles without a residual stores under the
+// row and token bounds; a call with one, and 256 x 128 tiles, take the
+// branch-free buffer stores (fp16, PLAIN against those: 8192 x 2048 at 2048
+// tokens 70.4 us against 75.3, at 4096 136 against 149, but with a residual 94
+// against 77; 4096 x 4096 at 2048 tokens on 256 x 128 tiles 81 against 79).
 // ---------------------------------------------------------------------------
-template <int DT, int EPI, int TNB, int WB>
+template <int DT, int EPI, int TNB, int WB, bool PLAIN>
 __global__ __launch_bounds__(256 * (1 + TNB), 1) void k_gemm_ws(GemmParams a) {
   static_assert(EPI == EPI_NONE || EPI == EPI_READY, "plain and semi-fused epilogues");
   extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -773,19 +778,34 @@ __global__ __launch_bounds__(256 * (1 + TNB), 1) void k_gemm_ws(GemmParams a) {
     }
   }
 
-  const rsrc_t ry = make_rsrc(a.y, (uint32_t)M * N * 2), rres = make_rsrc(a.res, (uint32_t)M * N * 2);
+  if constexpr (PLAIN) {
 #pragma unroll
-  for (int i = 0; i < FM32; ++i)
+    for (int i = 0; i < FM32; ++i)
 #pragma unroll
-    for (int j = 0; j < FN32; ++j)
-      store_results<DT, 16>(
-          ry, rres, a.res != nullptr,
-          [&](int e) {
-            const int n = n0 + wn * 64 + 32 * j + l32;
-            const int m = m0 + wm * 128 + 32 * i + 8 * (e >> 2) + 4 * lh + (e & 3);
-            return n < N && m < M ? ((uint32_t)m * N + n) * 2 : kOOB;
-          },
-          [&](int e) { return acc[i][j][e]; });
+      for (int j = 0; j < FN32; ++j) {
+        const int n = n0 + wn * 64 + 32 * j + l32;
+        if (n >= N) continue;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+          const int m = m0 + wm * 128 + 32 * i + 8 * (e >> 2) + 4 * lh + (e & 3);
+          if (m < M) a.y[(size_t)m * N + n] = f2act<DT>(acc[i][j][e]);
+        }
+      }
+  } else {
+    const rsrc_t ry = make_rsrc(a.y, (uint32_t)M * N * 2), rres = make_rsrc(a.res, (uint32_t)M * N * 2);
+#pragma unroll
+    for (int i = 0; i < FM32; ++i)
+#pragma unroll
+      for (int j = 0; j < FN32; ++j)
+        store_results<DT, 16>(
+            ry, rres, a.res != nullptr,
+            [&](int e) {
+              const int n = n0 + wn * 64 + 32 * j + l32;
+              const int m = m0 + wm * 128 + 32 * i + 8 * (e >> 2) + 4 * lh + (e & 3);
+              return n < N && m < M ? ((uint32_t)m * N + n) * 2 : kOOB;
+            },
+            [&](int e) { return acc[i][j][e]; });
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -832,21 +852,20 @@ hipError_t SPEAR_W(launch_gemm)(int epi, const GemmParams& p, hipStream_t st) {
     // reuses the space for v_hi, v_lo [256][72] and B [rows][72]
     const size_t lws = std::max((size_t)2 * TM * kGemmTK * 2 + (size_t)2 * 128 * tnb * kGemmLdsRow * 2,
                                 (size_t)(2 * TM + 128 * tnb) * kGemmLdsRow * 2);
-#define SPEAR_GEMM_WS(E, B)                                                               \
-  do {                                                                                    \
-    hipError_t err = allow_lds(k_gemm_ws<DTC, E, B, SPEAR_WB>, lws);                      \
-    if (err != hipSuccess) return err;                                                    \
-    hipLaunchKernelGGL((k_gemm_ws<DTC, E, B, SPEAR_WB>), dim3(gws), dim3(256 * (1 + B)), lws, st, p); \
-  } while (0)
-    if (tnb == 2) {
-      if (epi == EPI_NONE) SPEAR_GEMM_WS(EPI_NONE, 2);
-      else SPEAR_GEMM_WS(EPI_READY, 2);
-    } else {
-      if (epi == EPI_NONE) SPEAR_GEMM_WS(EPI_NONE, 1);
-      else SPEAR_GEMM_WS(EPI_READY, 1);
-    }
-#undef SPEAR_GEMM_WS
-    return hipGetLastError();
+    const auto go = [&](auto kern) {
+      hipError_t err = allow_lds(kern, lws);
+      if (err != hipSuccess) return err;
+      hipLaunchKernelGGL(kern, dim3(gws), dim3(256 * (1 + tnb)), lws, st, p);
+      return hipGetLastError();
+    };
+    if (tnb == 1)
+      return epi == EPI_NONE ? go(k_gemm_ws<DTC, EPI_NONE, 1, SPEAR_WB, false>)
+                             : go(k_gemm_ws<DTC, EPI_READY, 1, SPEAR_WB, false>);
+    if (p.res)
+      return epi == EPI_NONE ? go(k_gemm_ws<DTC, EPI_NONE, 2, SPEAR_WB, false>)
+                             : go(k_gemm_ws<DTC, EPI_READY, 2, SPEAR_WB, false>);
+    return epi == EPI_NONE ? go(k_gemm_ws<DTC, EPI_NONE, 2, SPEAR_WB, true>)
+                           : go(k_gemm_ws<DTC, EPI_READY, 2, SPEAR_WB, true>);
   }
   if (p.tmw == 4) {
     if (epi == EPI_NONE) SPEAR_GEMM_GO(EPI_NONE, 4);

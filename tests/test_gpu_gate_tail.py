@@ -68,3 +68,52 @@ def test_tanh_gate_shapes(M, rank, h, path, dt):
     L = scaled_ec(zero_weight(L), 30)
     log(f"tanh M={M} r={rank} h={h} path={path} dt={dt}")
     assert_parity(gpu_y(L, path=path), O.w4ec_linear(L), f"tanh path={path}")
+
+
+# (roles, M, N, K, slices): every GEMM's epilogue, whole and ragged tiles; the
+# 256 x 256 tiles store a call without a residual otherwise than one with it
+RES = [(1, 70, 200, 1024, 2), (1, 300, 136, 1024, 1), (2, 300, 200, 1024, 1), (2, 256, 128, 512, 1), (3, 512, 256, 512, 1),
+       (3, 257, 300, 1024, 1), (3, 300, 1000, 1024, 1), (4, 20, 200, 1024, 1), (4, 64, 130, 1024, 2), (4, 96, 256, 2048, 4),
+       (4, 300, 136, 1024, 1)]
+
+
+@pytest.mark.parametrize("roles,M,N,K,slices", RES)
+@pytest.mark.parametrize("rank", [0, 20])
+@pytest.mark.parametrize("dt", [S.F16, S.BF16])
+def test_residual_epilogues(roles, M, N, K, slices, rank, dt):
+    """A residual of zeros changes no value, a random one meets the oracle,
+    and nothing is written past the last row."""
+    from paper_2606_11244_amd import spear as sp
+    L = S.make_layer(M=M, N=N, K=K, group_size=128, rank=rank, act_dtype=dt, seed=M + N, ec_std=0.05)
+    res = S.make_tail(L, seed=2)["residual"]
+    tdt = sp._TORCH_DT[dt]
+    dl = sp.DeviceLayer(L)
+    prob = dl.problem(force_path=4)
+    y = torch.full((M + 4, N), 7.0, dtype=tdt, device="cuda")
+
+    def call(r):
+        y.fill_(7.0)
+        if r is None:
+            (dl.run_ec if rank else dl.run_w4)(prob, ws, y=y[:M])
+        else:
+            dl.run_tail(prob, ws, residual=r, y=y[:M], with_ec=rank > 0)
+        torch.cuda.synchronize()
+        assert torch.all(y[M:] == 7.0)
+        return y[:M].clone()
+
+    sp.set_gemm_tile(256 if roles in (2, 3) else 0)
+    sp.set_gemm_slices(slices)
+    sp.set_gemm_roles(roles)
+    try:
+        log(f"residual roles={roles} M={M} N={N} K={K} S={slices} r={rank} dt={dt}")
+        ws = sp.allocate_workspace(prob, rank > 0)
+        plain = call(None)
+        assert torch.equal(plain, call(torch.zeros_like(plain)))
+        got = call(torch.from_numpy(res.view(np.int16)).view(tdt).cuda())
+    finally:
+        sp.set_gemm_roles(0)
+        sp.set_gemm_slices(0)
+        sp.set_gemm_tile(0)
+    ref = O.w4ec_linear(L) if rank else O.w4_linear_layer(L)
+    assert_parity(plain.double().cpu().numpy(), ref, "plain")
+    assert_parity(got.double().cpu().numpy(), ref + S.from_bits(res, dt).astype(np.float64), "residual")
