@@ -162,7 +162,7 @@ def _pass_of(name, grid):
         return "decode"
     if "k_gemm" in name:
         return "prefill"
-    if "k_ec<" in name:
+    if re.search(r"k_ec(_group)?<", name):
         return "decode" if grid < 256 else "prefill"
     return None
 
@@ -279,9 +279,9 @@ def main70(argv):
         f.write("\n".join(lines))
     out = {"kernel_source_hash": kernel_source_hash(),
            "workload": "llama-2-70b-shaped model, decode M=1 and prefill M=4096 passes",
-           "decode_kernel": "every decode-pass launch (k_gemv*, k_ec with < 256 workgroups)",
+           "decode_kernel": "every decode-pass launch (k_gemv*, k_ec* with < 256 workgroups)",
            "decode_bytes_per_launch": round(dec),
-           "prefill_kernel": "every prefill-pass launch (k_gemm*, k_ec with >= 256 workgroups)",
+           "prefill_kernel": "every prefill-pass launch (k_gemm*, k_ec* with >= 256 workgroups)",
            "prefill_bytes_per_launch": round(pre),
            "read_scale": round(k_f, 4), "write_scale": round(k_w, 4),
            "commands": [tcmd, fcmd, wcmd] + ([c.strip() for c in scmd.split(" | ")] if sq else [])}
