@@ -168,7 +168,7 @@ __device__ __forceinline__ void ec_gate_tile(const EcParams& e, int cnt, const f
 // and publishes v: as fp32 (read by a later kernel), as act-dtype hi/lo parts
 // (the prefill GEMM epilogue) and/or as tagged words in one copy per XCD (the
 // fused kernel's consumers).
-template <int DT, int IPP>
+template <int DT, int IPP, bool PRE>
 __device__ __forceinline__ void ec_producer(const EcParams& e, int b, uint32_t gen, char* smem) {
   __shared__ int s_last;
   const int tid = threadIdx.x, nthr = blockDim.x;
@@ -191,8 +191,10 @@ __device__ __forceinline__ void ec_producer(const EcParams& e, int b, uint32_t g
 
   // the tanh-MLP gate's parameters, which only the token tile's last workgroup
   // reads, after everything else: requested here (up to 16 KB of each matrix)
-  // so that its reads find them in this XCD's L2 instead of in memory
-  if (e.gate == GATE_TANH) {
+  // so that its reads find them in this XCD's L2 instead of in memory. (Not
+  // among the fused GEMV's producers, whose registers it costs: 4096 x 14336 at
+  // four tokens 26.9 us without it, 27.9 with it.)
+  if (PRE && e.gate == GATE_TANH) {
     const rsrc_t r1 = make_rsrc(e.W1, (uint32_t)e.h * e.r * 2), r2 = make_rsrc(e.W2, (uint32_t)e.h * e.r * 2);
     u32x4 t[4];
 #pragma unroll
@@ -291,7 +293,7 @@ __device__ __forceinline__ void ec_producer(const EcParams& e, int b, uint32_t g
 template <int DT, int IPP>
 __global__ __launch_bounds__(512) void k_ec(EcParams e) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  ec_producer<DT, IPP>(e, blockIdx.x, 0u, smem);
+  ec_producer<DT, IPP, true>(e, blockIdx.x, 0u, smem);
 }
 
 // The same of up to kGroupMax layers in one launch (the layers of a group share
@@ -305,7 +307,7 @@ __global__ __launch_bounds__(512) void k_ec_group(EcGroup g) {
 #pragma unroll
   for (int j = 1; j < kGroupMax; ++j)
     if (j < g.n && b >= g.start[j]) i = j;
-  ec_producer<DT, IPP>(g.p[i], b - g.start[i], 0u, smem);
+  ec_producer<DT, IPP, true>(g.p[i], b - g.start[i], 0u, smem);
 }
 
 // Naive chain, gate launch: reads u [M][R1] and writes v [M][r].
@@ -751,8 +753,14 @@ __device__ void ec_wave(const GemvParams& a, uint32_t gen, char* smem, int n0, b
 //
 // Fused variant: the first n_prod blocks of the grid are EC producers; the
 // others' EC waves wait for what they publish.
+//
+// SPLIT: with the split-K reduction. Calls of one token tile in one K-slice run
+// a build without it: its code, though never reached there, changed the
+// registers and the schedule of the whole kernel (local variant 2048 x 2048, rank
+// 16, bf16, one token: 8.4 us with it, 7.4 without; 4-bit product 8192 x 8192 at
+// one token 12.0 and 11.5; producer-fused 8192 x 8192, rank 32, 18.0 and 17.3).
 // ---------------------------------------------------------------------------
-template <int DT, int MT, int RT, int EPI, int WB, int NST = 2>
+template <int DT, int MT, int RT, int EPI, int WB, int NST, bool SPLIT>
 __device__ __forceinline__ void gemv_body(const GemvParams& a, int bid, uint32_t gen, char* smem) {
   __shared__ int s_flag;
   constexpr bool kEC = EPI == EPI_READY || EPI == EPI_FUSED;  // with an EC wave
@@ -766,7 +774,8 @@ __device__ __forceinline__ void gemv_body(const GemvParams& a, int bid, uint32_t
   constexpr int RB = 16 * RT;
   const int M = a.M, N = a.N, K = a.K, G = a.G;
   const int IT = K / kIterK;
-  const int rg = bid / a.S, s = bid - (bid / a.S) * a.S;
+  const int S = SPLIT ? a.S : 1;
+  const int rg = bid / S, s = bid - rg * S;
   const int n0 = rg * RB;
   const int it_blk = s * a.ips;
   const int it_end = min(IT, it_blk + a.ips);
@@ -1218,7 +1227,7 @@ __device__ __forceinline__ void gemv_body(const GemvParams& a, int bid, uint32_t
   // a token also sums that token's gate logit and writes v_j directly
   // (EPI_LOCAL, below), saving a pass and a barrier.
   float* v_loc = u_loc + 16 * MT * R1p;
-  const bool v_direct = a.S == 1 && a.ec.gate != GATE_TANH;
+  const bool v_direct = S == 1 && a.ec.gate != GATE_TANH;
   if constexpr (kLoc) {
     // tile 0: column j < r is u_j; tile 1: column 0 is the gate logit w_g x
     for (int e = tid; e < 256 * kLocalTiles * MT; e += blockDim.x) {
@@ -1263,10 +1272,9 @@ __device__ __forceinline__ void gemv_body(const GemvParams& a, int bid, uint32_t
   __syncthreads();
 
   // ---- cross-block split-K reduction: the last arriver sums the slices in order
-  // (in the local variant out of the straight line of the unsplit call: 8192 x
-  // 2048 at 16 tokens 10.6 -> 10.3 us; the fused one is faster as written, 19.1
-  // us against 19.6 for 8192 x 8192 at one token)
-  if (kLoc ? __builtin_expect(a.S > 1, 0) : a.S > 1) {
+  // (the local variant is faster with it out of the straight line, 2048 x 8192,
+  // rank 16, at 16 tokens in several slices 14.5 us against 14.7)
+  if (kLoc ? __builtin_expect(S > 1, 0) : S > 1) {
     for (int e = tid; e < RB * M; e += blockDim.x) {
       const int m = e / RB, row = e - m * RB;
       if (n0 + row < N) st_agent(a.ypart + ((size_t)s * M + m) * N + n0 + row, yacc[m * YS + row]);
@@ -1310,7 +1318,8 @@ __device__ __forceinline__ void gemv_body(const GemvParams& a, int bid, uint32_t
   // EPI_LOCAL: v = alpha g(x) (.) A x for every token (g the sigmoid of the
   // gate row's sum plus b_g, or one; or the tanh-MLP gate of u, whose hidden
   // layer takes the LDS after v), then y += v B^T in fp32 below
-  if (kLoc && !v_direct && __builtin_expect(a.ec.gate == GATE_TANH, 0)) {
+  if (kLoc && !v_direct &&
+      (SPLIT ? __builtin_expect(a.ec.gate == GATE_TANH, 0) : a.ec.gate == GATE_TANH)) {
     // LDS after v: the hidden layer (cap x h floats)
     tanh_gate_tokens<DT>(M, r, a.ec.h, u_loc, R1p, a.ec.W1, a.ec.b1, a.ec.W2, a.ec.b2, a.ec.alpha,
                          v_loc + 16 * MT * r, local_tanh_cap(M, a.ec.h), v_loc, r);
@@ -1389,7 +1398,7 @@ constexpr int gemv_min_waves(int MT, int RT, int EPI) {
   return MT == 1 && RT <= 2 && EPI <= EPI_FUSED ? 4 : 1;
 }
 
-template <int DT, int MT, int RT, int EPI, int WB, int NST>
+template <int DT, int MT, int RT, int EPI, int WB, int NST, bool SPLIT>
 __global__ __launch_bounds__(kGemvMaxThreads, gemv_min_waves(MT, RT, EPI)) void k_gemv(GemvParams a) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   int bid = blockIdx.x;
@@ -1398,20 +1407,20 @@ __global__ __launch_bounds__(kGemvMaxThreads, gemv_min_waves(MT, RT, EPI)) void 
     // the first n_prod workgroups are the EC producers
     gen = (uint32_t)(__hip_atomic_load(gen_counter(a, bid), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> 32);
     if (bid < a.n_prod) {
-      ec_producer<DT, 1>(a.ec, bid, gen, smem);
+      ec_producer<DT, 1, false>(a.ec, bid, gen, smem);
       fused_exit(a);
       return;
     }
     bid -= a.n_prod;
   }
-  gemv_body<DT, MT, RT, EPI, WB, NST>(a, bid, gen, smem);
+  gemv_body<DT, MT, RT, EPI, WB, NST, SPLIT>(a, bid, gen, smem);
 }
 
 // Several independent layer calls of one GEMV variant in one launch: member i
 // owns the workgroups [start[i], start[i+1]) and runs exactly the blocks its
 // own launch would run, so each member's output is the one its single call
 // writes. The member index is uniform over the workgroup.
-template <int DT, int MT, int RT, int EPI, int WB>
+template <int DT, int MT, int RT, int EPI, int WB, bool SPLIT>
 __global__ __launch_bounds__(kGemvMaxThreads, gemv_min_waves(MT, RT, EPI)) void k_gemv_group(GemvGroup g) {
   static_assert(EPI != EPI_FUSED, "grouped launches take the variants without cross-launch state");
   extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -1420,7 +1429,7 @@ __global__ __launch_bounds__(kGemvMaxThreads, gemv_min_waves(MT, RT, EPI)) void 
 #pragma unroll
   for (int j = 1; j < kGroupMax; ++j)
     if (j < g.n && b >= g.start[j]) i = j;
-  gemv_body<DT, MT, RT, EPI, WB>(g.p[i], b - g.start[i], 0u, smem);
+  gemv_body<DT, MT, RT, EPI, WB, 2, SPLIT>(g.p[i], b - g.start[i], 0u, smem);
 }
 
 // ---------------------------------------------------------------------------
@@ -1484,10 +1493,15 @@ hipError_t SPEAR_D(launch_ec_up_acc)(const float* v, const uint16_t* B, const in
 template <int DT, int MT, int RT, int EPI, int NST>
 static hipError_t gemv_launch_one(const GemvParams& p, int grid, int block, size_t lds,
                                   hipStream_t st) {
-  hipError_t err = allow_lds(k_gemv<DT, MT, RT, EPI, SPEAR_WB, NST>, lds);
-  if (err != hipSuccess) return err;
-  hipLaunchKernelGGL((k_gemv<DT, MT, RT, EPI, SPEAR_WB, NST>), dim3(grid), dim3(block), lds, st, p);
-  return hipGetLastError();
+  const auto go = [&](auto kern) {
+    hipError_t err = allow_lds(kern, lds);
+    if (err != hipSuccess) return err;
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(block), lds, st, p);
+    return hipGetLastError();
+  };
+  if constexpr (MT == 1 && NST == 2)
+    if (p.S == 1) return go(k_gemv<DT, MT, RT, EPI, SPEAR_WB, NST, false>);
+  return go(k_gemv<DT, MT, RT, EPI, SPEAR_WB, NST, true>);
 }
 
 // Pipeline depths compiled in: 2 everywhere; 4 for one token tile on the
@@ -1549,13 +1563,16 @@ static hipError_t gemv_group_launch(int epi, const GemvGroup& g, int block, size
                                     hipStream_t st) {
   constexpr int WB = SPEAR_WB;
   const int grid = g.start[g.n];
-#define SPEAR_GEMV_GROUP_GO(E)                                                                   \
-  case E: {                                                                                      \
-    hipError_t err = allow_lds(k_gemv_group<DT, MT, RT, E, WB>, lds);                            \
-    if (err != hipSuccess) return err;                                                           \
-    hipLaunchKernelGGL((k_gemv_group<DT, MT, RT, E, WB>), dim3(grid), dim3(block), lds, st, g);  \
-    break;                                                                                       \
-  }
+  bool split = MT > 1;  // a member in several K-slices
+  for (int i = 0; i < g.n; ++i) split |= g.p[i].S > 1;
+  const auto go = [&](auto kern) {
+    hipError_t err = allow_lds(kern, lds);
+    if (err != hipSuccess) return err;
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(block), lds, st, g);
+    return hipGetLastError();
+  };
+#define SPEAR_GEMV_GROUP_GO(E) \
+  case E: return split ? go(k_gemv_group<DT, MT, RT, E, WB, true>) : go(k_gemv_group<DT, MT, RT, E, WB, MT != 1>);
   switch (epi) {
     SPEAR_GEMV_GROUP_GO(EPI_NONE)
     SPEAR_GEMV_GROUP_GO(EPI_READY)
@@ -1564,7 +1581,6 @@ static hipError_t gemv_group_launch(int epi, const GemvGroup& g, int block, size
     default: return hipErrorInvalidValue;
   }
 #undef SPEAR_GEMV_GROUP_GO
-  return hipGetLastError();
 }
 
 hipError_t SPEAR_W(launch_gemv_group)(int MT, int RT, int epi, const GemvGroup& g,
