@@ -1,4 +1,4 @@
-"""GPU parity of the GEMM that keeps the codes in registers (17 to 128 tokens):
+"""GPU parity of the GEMM that keeps the codes in registers (17 to 384 tokens):
 its token-tile widths, K-slices and remainders, ragged rows, both code widths,
 the EC epilogue, and grouped calls that share its launch and the EC
 pre-kernel's, bit for bit the members' own calls."""
@@ -99,19 +99,13 @@ def test_ec_epilogue(forced, M, N, K, rank, slices, int8, dt):
     assert_parity(gpu_y(Z, path=4), O.w4ec_linear(Z), "EC term")
 
 
-@pytest.mark.parametrize("M,K,ranks", [
-    (24, 1024, (0, 0, 0)), (20, 1024, (32, 32, 32)), (24, 8192, (16, 0, 16)), (40, 2048, (64, 0, 64)),
-    (64, 1024, (24, 33, 0)), (90, 2048, (0, 32, 0)), (300, 1024, (32, 64, 32)), (8, 4096, (32, 32, 0)),
-    (20, 1024, (0, 32, 0)),
-    (1, 8192, (64, 64, 64)), (4, 8192, (64, 0, 64)), (16, 8192, (64, 20, 64)), (32, 8192, (32, 64, 32))])
-def test_group_is_the_members_own_calls(M, K, ranks):
-    """Products that share a launch, EC pre-kernels that share one (also where
-    the products do not: beyond 128 tokens), and producer-fused decode calls
-    whose projections move to the shared pre-kernel, alone and beside members that share nothing, on one workspace twice in a row."""
+def _group_check(M, K, ranks, Ns=(520, 128, 1100), launches=None, **kw):
+    """A group's outputs are the members' own calls' (bit for bit, on one
+    workspace twice in a row) and meet the oracle."""
     from paper_2606_11244_amd import spear as sp
     dls, members, alone = [], [], []
-    for i, (N, r) in enumerate(zip((520, 128, 1100), ranks)):
-        dl = sp.DeviceLayer(S.make_layer(M=M, N=N, K=K, group_size=128, rank=r, seed=M + i, ec_std=0.05))
+    for i, (N, r) in enumerate(zip(Ns, ranks)):
+        dl = sp.DeviceLayer(S.make_layer(M=M, N=N, K=K, rank=r, seed=M + i, ec_std=0.05, **dict(dict(group_size=128), **kw)))
         prob = dl.problem()
         ws = sp.allocate_workspace(prob, r > 0)
         y = torch.empty_like(dl.y)
@@ -119,7 +113,8 @@ def test_group_is_the_members_own_calls(M, K, ranks):
         dls.append(dl)
         alone.append(y)
         members.append(dl.member(prob, with_ec=r > 0))
-    log(f"group M={M} K={K} ranks={ranks} launches={sp.group_launches(members)}")
+    log(f"group M={M} K={K} ranks={ranks} Ns={Ns} {kw} launches={sp.group_launches(members)}")
+    assert launches is None or sp.group_launches(members) == launches
     ws = torch.zeros(max(256, sp.group_workspace(members)), dtype=torch.uint8, device="cuda")
     for _ in range(2):
         for dl in dls:
@@ -131,6 +126,45 @@ def test_group_is_the_members_own_calls(M, K, ranks):
     for dl, r in zip(dls, ranks):
         got = dl.y.float().cpu().numpy().astype(np.float64)
         assert_parity(got, O.w4ec_linear(dl.layer) if r else O.w4_linear_layer(dl.layer), "group")
+
+
+# (M, K, ranks, launches): the counts test_group.py derives on the host
+@pytest.mark.parametrize("M,K,ranks,launches", [
+    (24, 1024, (0, 0, 0), 1), (20, 1024, (32, 32, 32), 2), (24, 8192, (16, 0, 16), 2), (40, 2048, (64, 0, 64), 2),
+    (64, 1024, (24, 33, 0), 2), (90, 2048, (0, 32, 0), 2), (300, 1024, (32, 64, 32), 4), (8, 4096, (32, 32, 0), 3),
+    (20, 1024, (0, 32, 0), 2),
+    (1, 8192, (64, 64, 64), 2), (4, 8192, (64, 0, 64), 3), (16, 8192, (64, 20, 64), 2), (32, 8192, (32, 64, 32), 2)])
+def test_group_is_the_members_own_calls(M, K, ranks, launches):
+    """Products that share a launch, EC pre-kernels that share one (also where
+    the products do not: at 300 tokens of a small layer), and producer-fused
+    decode calls whose projections move to the shared pre-kernel, alone and
+    beside members that share nothing."""
+    _group_check(M, K, ranks, launches=launches)
+
+
+@pytest.mark.parametrize("kw", [
+    dict(act_dtype=S.BF16), dict(act_dtype=S.BF16, weight_bits=3, group_size=0), dict(weight_bits=3),
+    dict(act_dtype=S.BF16, ab_int8=True), dict(ab_int8=True, gate_kind=S.GATE_ONE),
+    dict(gate_kind=S.GATE_TANH_MLP, gate_hidden=72), dict(act_dtype=S.BF16, gate_kind=S.GATE_TANH_MLP, gate_hidden=128),
+    dict(act_dtype=S.BF16, gate_kind=S.GATE_ONE, weight_bits=3)])
+@pytest.mark.parametrize("M,K,ranks", [(8, 4096, (32, 24, 32)), (3, 8192, (64, 20, 64)), (20, 1024, (32, 0, 24)),
+                                       (40, 2048, (64, 33, 64))])
+def test_group_kinds(M, K, ranks, kw):
+    """The shared pre-kernel with the shared GEMV (8 tokens; 3 tokens, members
+    that are producer-fused alone) and with the shared k_gemm_r, over the
+    dtypes, code widths, factor formats and gates."""
+    _group_check(M, K, ranks, launches=2, **kw)
+
+
+@pytest.mark.parametrize("M", [4, 16])
+@pytest.mark.parametrize("kw", [dict(), dict(act_dtype=S.BF16, ab_int8=True)])
+def test_group_four_row_tiles(M, kw):
+    """Producer-fused members of four row tiles (more than 8192 rows, K 8192)
+    beside narrower ones, which are brought to four in the shared launch."""
+    from paper_2606_11244_amd import spear as sp
+    plans = [sp.dispatch_plan(sp.problem(M, N, 8192, 128, sp.F16, 64)) for N in (8224, 1100)]
+    assert [(p.path, p.tile_n) for p in plans] == [(sp.PATH_FUSED_GEMV, 64), (sp.PATH_FUSED_GEMV, 32)]
+    _group_check(M, 8192, (64, 64), Ns=(8224, 1100), launches=2, **kw)
 
 
 @pytest.mark.parametrize("M,N,K,rank", [
