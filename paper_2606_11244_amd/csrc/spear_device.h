@@ -271,8 +271,8 @@ __device__ __forceinline__ void bst16(rsrc_t r, uint32_t off, uint16_t v) {
 // The GEMMs' final store: CNT fp32 results of a lane at byte offsets off(i) of
 // y (kOOB: not stored), the residual added before the rounding. The residual
 // elements are all requested before the first is used, and neither loads nor
-// stores branch: with a branch and a wait per element the residual cost 86 us
-// of 568 on the 70B o module at 4096 tokens (RES_MEASURED).
+// stores branch: with a branch and a wait per element 8192 x 8192 at 4096 tokens
+// took 578 us with a residual (fp16), 507 without; this way 526.
 template <int DT, int CNT, class Off, class Val>
 __device__ __forceinline__ void store_results(rsrc_t ry, rsrc_t rres, bool has_res, Off off, Val val) {
   if (has_res) {  // uniform
@@ -368,27 +368,31 @@ __device__ __forceinline__ int gather_tagged(rsrc_t r, int n, Off off, uint32_t 
 
 // out(i, sum over q < P of the word at off(q, i)), i in [0, n), summed in
 // slice order. The slices lie at the device coherence point, a memory round
-// trip away, so each thread sums two elements at a time with eight slices of
+// trip away, so each thread sums two elements at a time with U slices of
 // both in flight and nothing goes through LDS (a staged copy of bounded size
 // took six dependent round trips for a 16-token tile of rank 64 in eight
-// slices: EC_SUM_MEASURED). Every thread of the block calls it; it ends with a
-// barrier.
-template <class Off, class Out>
+// slices: 1024 x 8192 at 16 tokens, producer-fused, 22.3 us against 19.3).
+// U: eight where the slices are many (the EC projection's); four for the
+// GEMV's few K-slices, where eight issued mostly loads past the last one (local
+// variant, rank 16, bf16: 1024 x 4096 at two tokens staged 11.8 us, eight 12.0,
+// four 11.3; 2048 x 8192 at 16 tokens 15.1, 14.5, 13.6).
+// Every thread of the block calls it; it ends with a barrier.
+template <int U = 8, class Off, class Out>
 __device__ __forceinline__ void sum_slices(rsrc_t r, int P, int n, Off off, Out out) {
   const int nthr = blockDim.x;
   for (int i0 = threadIdx.x; i0 < n; i0 += 2 * nthr) {
     const int i1 = i0 + nthr;
     float a = 0.f, b = 0.f;
-    for (int q0 = 0; q0 < P; q0 += 8) {
-      uint32_t wa[8], wb[8];
+    for (int q0 = 0; q0 < P; q0 += U) {
+      uint32_t wa[U], wb[U];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
+      for (int u = 0; u < U; ++u) {
         const bool ok = q0 + u < P;
         wa[u] = bld32c(r, ok ? off(q0 + u, i0) : kOOB);
         wb[u] = bld32c(r, ok && i1 < n ? off(q0 + u, i1) : kOOB);
       }
 #pragma unroll
-      for (int u = 0; u < 8; ++u)
+      for (int u = 0; u < U; ++u)
         if (q0 + u < P) {
           a += __uint_as_float(wa[u]);
           b += __uint_as_float(wb[u]);

@@ -1296,7 +1296,7 @@ __device__ __forceinline__ void gemv_body(const GemvParams& a, int bid, uint32_t
     }
     // every slice's [M][RB] partial, summed in slice order
     const rsrc_t rp = make_rsrc(a.ypart, (uint32_t)a.S * M * N * 4);
-    sum_slices(rp, a.S, M * RB, [&](int q, int i) {
+    sum_slices<4>(rp, a.S, M * RB, [&](int q, int i) {
       const int m = i / RB, row = i - m * RB;
       return n0 + row < N ? (uint32_t)(((size_t)q * M + m) * N + n0 + row) * 4u : kOOB;
     }, [&](int i, float v) {
@@ -1306,7 +1306,7 @@ __device__ __forceinline__ void gemv_body(const GemvParams& a, int bid, uint32_t
     if constexpr (kLoc) {
       // this row group's slices' [A; w_g] x, summed in slice order
       const rsrc_t re = make_rsrc(a.eupart, (uint32_t)((size_t)a.N / RB + 1) * a.S * M * R1 * 4);
-      sum_slices(re, a.S, M * R1, [&](int q, int i) {
+      sum_slices<4>(re, a.S, M * R1, [&](int q, int i) {
         return (uint32_t)(((size_t)(rg * a.S + q) * M) * R1 + i) * 4u;
       }, [&](int i, float v) {
         const int m = i / R1, j = i - m * R1;
