@@ -90,8 +90,9 @@ enum {
   SPEAR_PATH_FUSED_GEMV = 1,     /* one kernel: split-K 4-bit GEMV; the same grid
                                     computes A x and the gate, and the epilogue
                                     adds B (g (.) A x). Decode: up to 64
-                                    tokens; AUTO's choice up to 32 where the
-                                    local variant does not apply              */
+                                    tokens; AUTO's choice up to 32 where
+                                    neither the local variant applies nor the
+                                    semi-fused pair is the faster one         */
   SPEAR_PATH_FUSED_MFMA = 2,     /* one kernel: the 4-bit MFMA GEMM also projects
                                     its activation tiles on A and w_g (split
                                     over K with the product when the tile grid
@@ -100,15 +101,21 @@ enum {
                                     every gate (else SPEAR_E_UNSUPPORTED).
                                     AUTO picks it for
                                     M > 32 while the grid has at most 256
-                                    128 x 128 tiles and the GEMM would not
-                                    take 256-token tiles                       */
+                                    128 x 128 tiles, the GEMM would not
+                                    take 256-token tiles, and the semi-fused
+                                    pair on k_gemm_r (up to 384 tokens) is not
+                                    the faster one by its rule on sizes        */
   SPEAR_PATH_UNFUSED_CHAIN = 3,  /* naive split: 4-bit GEMM, then separate
                                     projection, gate and reprojection+accumulate
                                     kernels (the baseline of section 4.1)      */
   SPEAR_PATH_UNFUSED_2K = 4,     /* semi-fused: EC pre-kernel (A x, gate) then
                                     the 4-bit GEMM/GEMV whose epilogue adds
                                     B (g (.) A x). AUTO's choice for M > 32
-                                    otherwise                                  */
+                                    otherwise, from 17 tokens on k_gemm_r by
+                                    its rule on sizes, and at decode on the
+                                    GEMV where the producer-fused variant is
+                                    slower (one token on very deep layers, 2
+                                    to 32 tokens where K is at most 4096)      */
   SPEAR_PATH_OVERLAP_2K = 6,     /* semi-fused with the EC on a second stream
                                     (section 4.1's prefill design): the EC
                                     pre-kernel runs on a library-owned side
@@ -127,7 +134,8 @@ enum {
                                     workgroups beyond the split-K reduction);
                                     rank <= 16, every gate, M <= 32. AUTO
                                     picks it where it
-                                    applies, otherwise SPEAR_PATH_FUSED_GEMV   */
+                                    applies (but for one token on narrow
+                                    layers at least 8192 deep)                 */
 };
 
 typedef struct {
@@ -283,18 +291,28 @@ spear_status_t spear_w4ec_linear_tail(const spear_problem_t* prob, const void* x
  * weights (section 4.1: launch overhead, not arithmetic, dominates the decode
  * path), and the modules of a transformer block that read the same hidden
  * state (q, k, v; gate, up) are independent calls. A group runs up to
- * SPEAR_GROUP_MAX such calls, and the members that take one single-launch
- * GEMV variant share one launch: the 4-bit product alone (ec NULL) or the
- * fused local path (M <= 32, an elementwise gate and rank <= 16, where the
- * planner takes that path), with the same act dtype, code width and token
- * tiles. Of several such sets the largest (at least two members) shares the
- * launch. Its members are re-planned to one row-tile count where their own
- * plans differ and the re-plan leaves every member's K-slices and per-wave
- * work unchanged (the largest such count); local-EC members whose blocks
- * together exceed one round on the GPU then take four row tiles each under
- * the same condition. The other members (other variants, token counts
- * beyond the GEMV, a tiling that cannot be shared) run first, one after
- * another in array order on the same stream, each on its own planned path.
+ * SPEAR_GROUP_MAX such calls, and members of the same act dtype (and, where
+ * they read codes, code width) share launches:
+ * - one launch for the members that take one single-launch GEMV variant, the
+ *   4-bit product alone (ec NULL) or the fused local path, with the same
+ *   token tiles. Of several such sets the largest (at least two members)
+ *   shares the launch. Its members are re-planned to one row-tile count where
+ *   their own plans differ and the re-plan leaves every member's K-slices and
+ *   per-wave work unchanged (the largest such count); local-EC members whose
+ *   blocks together exceed one round on the GPU then take four row tiles each
+ *   under the same condition.
+ * - of the others, the members on k_gemm_r with the same token tile (products
+ *   alone and semi-fused members) share one launch, the semi-fused members
+ *   and the producer-fused ones (SPEAR_PATH_FUSED_GEMV on AUTO) on the
+ *   GEMV with the same token tiles and waves share one, on the set's largest
+ *   row-tile count, and the EC pre-kernels of all semi-fused members share
+ *   one (per workgroup shape). A producer-fused member of such a set has its
+ *   projection, in the slices of its own call, in the shared pre-kernel; one
+ *   that forces SPEAR_PATH_FUSED_GEMV stays on it.
+ * - every other member runs on its own planned path.
+ * Members that share nothing run first, in array order; then the shared
+ * pre-kernels, the k_gemm_r and EC GEMV launches, and the first set's launch
+ * last, all on the same stream.
  * Either way each member's Y is exactly (bit for bit) what its own
  * spear_w4ec_linear or spear_w4_linear call writes. */
 #define SPEAR_GROUP_MAX 4
@@ -322,9 +340,10 @@ typedef struct {
 spear_status_t spear_group_workspace(int32_t n, const spear_layer_call_t* calls, size_t* out_bytes);
 
 /* Kernel launches a spear_w4ec_linear_group call with these members makes:
- * one for the members that share a launch, plus each other member's own
- * launch count (spear_plan_t.num_launches). Host-only. Errors as in
- * spear_group_workspace. */
+ * one for each shared launch (see above), one for the 4-bit product of a
+ * semi-fused member that shares its pre-kernel alone, and the own launch count
+ * (spear_plan_t.num_launches) of each member that shares nothing. Host-only.
+ * Errors as in spear_group_workspace. */
 spear_status_t spear_group_launches(int32_t n, const spear_layer_call_t* calls, int32_t* out_launches);
 
 /* Runs the n members (see above) on hip_stream. Validation of every member
