@@ -842,8 +842,9 @@ def main():
             "kernel": ("every launch of the decode pass: the 4-bit GEMV (k_gemv, EPI_NONE; "
                        "k_gemv_group where modules of a grouped call without an EC share a "
                        "launch) on the modules without an EC, the producer-fused W4+EC GEMV (k_gemv, "
-                       "EPI_FUSED) on those with one, and on the 28672-deep down modules the EC "
-                       "pre-kernel k_ec + k_gemv (EPI_READY)"),
+                       "EPI_FUSED) on those with one, on the 28672-deep down modules the EC "
+                       "pre-kernel k_ec + k_gemv (EPI_READY), and where modules of a grouped "
+                       "call with an EC share launches k_ec_group + k_gemv_group (EPI_READY)"),
             "achieved": round(dec_bytes / dec_launches / (dec_s / dec_launches) / 1e9, 2),
             "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": round(dec_gbs / HBM_PEAK_GBS, 4),
